@@ -288,8 +288,8 @@ int cs_clover_create(cs_gauge g, double kappa, double csw, void* stream, cs_clov
         return fail(CS_ERR_ALLOC, "could not allocate the clover term");
     }
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = cs::launch_clover_build(g->g, g->links[cs::P_F64], kappa, csw, c->c64, c->c32, s);
-    if (e == hipSuccess) e = cs::launch_clover_invert(g->g, c->c64, c->ci64, c->ci32, s);
+    hipError_t e = cs::launch_clover_build(g->g, g->links[cs::P_F64], kappa, csw, c->c64, s);
+    if (e == hipSuccess) e = cs::launch_clover_invert(g->g, c->c64, c->c32, c->ci64, c->ci32, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         cs_clover_destroy(c);

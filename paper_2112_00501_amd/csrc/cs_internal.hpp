@@ -395,12 +395,15 @@ struct ProfScope {
 // setup.hip
 hipError_t launch_import_links(const Geom& g, const void* U_canonical, void* l64, void* l32,
                                void* l16, void* lbf16, hipStream_t s);
-hipError_t launch_clover_build(const Geom& g, const void* links64, double kappa, double csw,
-                               void* c64, void* c32, hipStream_t s);
+// C = 1 + T in FP64 (its FP32 copy is written by launch_clover_invert)
+hipError_t launch_clover_build(const Geom& g, const void* links64, double kappa, double csw, void* c64,
+                               hipStream_t s);
 // canonical [V][12][12]: T (inverse false) or the packed matrix itself (true)
 hipError_t launch_clover_export(const Geom& g, const void* c64, void* dst, bool inverse, hipStream_t s);
-// (1 + T)^-1 per site, packed like the clover term, FP64 and FP32
-hipError_t launch_clover_invert(const Geom& g, const void* c64, void* ci64, void* ci32, hipStream_t s);
+// (1 + T)^-1 per site, packed like the clover term, FP64 and FP32, and the
+// FP32 copy c32 of the clover term itself
+hipError_t launch_clover_invert(const Geom& g, const void* c64, void* c32, void* ci64, void* ci32,
+                                hipStream_t s);
 hipError_t launch_field_import(const Geom& g, int prec, void* dst, const void* src, int nrhs,
                                hipStream_t s);
 hipError_t launch_field_export(const Geom& g, int prec, void* dst, const void* src, int nrhs,
