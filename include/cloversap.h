@@ -459,7 +459,7 @@ int cs_bicgstab_solve_mg(cs_gauge g, cs_clover c, cs_mg m, const cs_solver_param
  *            gradient G = 2 i (sum_a g_a T^a) U, which satisfies
  *            dL = Re tr(G^dag dU) for every dU = i X U, X Hermitian
  *            traceless (the gradient of any SU(3)-valued parametrisation).
- * Needs 864 bytes per site of device workspace (kept with the clover
+ * Needs 432 bytes per site of device workspace (kept with the clover
  * handle).  Asynchronous on the stream. */
 int cs_force(cs_gauge g, cs_clover c, const void* x, const void* y, double* g_lie,
              void* grad_U, void* stream);
@@ -467,9 +467,9 @@ int cs_force(cs_gauge g, cs_clover c, const void* x, const void* y, double* g_li
 /* cs_force for callers that cannot allocate device memory (code under HIP
  * graph capture, serving loops, harnesses that forbid allocation): the same
  * kernels and results, with the insertion-matrix workspace taken from a
- * fixed 128 MiB device array of the library instead of memory allocated on
+ * fixed 64 MiB device array of the library instead of memory allocated on
  * the first call.  No device memory is allocated or freed.  The lattice may
- * have at most 155,344 sites (864 bytes each; a 16^3 x 32 lattice fits,
+ * have at most 155,344 sites (432 bytes each; a 16^3 x 32 lattice fits,
  * 32^3 x 64 does not): larger lattices return CS_ERR_INVALID.  Every GPU
  * that runs it holds its own copy of the array until the process ends (its
  * address is looked up on the first call on that device).  The workspace is

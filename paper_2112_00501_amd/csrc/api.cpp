@@ -47,7 +47,7 @@ struct cs_clover_s {
     std::unique_ptr<cs::GcrWork> work;
     std::vector<std::unique_ptr<cs::GcrWork>> group_work;  // one per concurrent group of right-hand sides
     std::unique_ptr<cs::BicgWork> bicg;
-    void* force_H = nullptr;   // insertion matrices of the force, 864 B/site
+    void* force_H = nullptr;   // insertion matrices of the force, FORCE_SITE_BYTES a site
     void* dag_tmp = nullptr;   // FP64 fields for the adjoint solve
     int dag_tmp_nrhs = 0;
     // autotuned multi-right-hand-side launch shapes, keyed by (precision, nrhs)
@@ -836,9 +836,9 @@ int cs_force(cs_gauge g, cs_clover c, const void* x, const void* y, double* g_li
     if (st) return st;
     if (!x || !y) return fail(CS_ERR_NULL, "x and y must be non-NULL");
     if (!g_lie && !grad_U) return fail(CS_ERR_NULL, "at least one of g_lie and grad_U must be non-NULL");
-    if (!c->force_H && hipMalloc(&c->force_H, (size_t)864 * g->g.V) != hipSuccess) {
+    if (!c->force_H && hipMalloc(&c->force_H, cs::FORCE_SITE_BYTES * (size_t)g->g.V) != hipSuccess) {
         c->force_H = nullptr;
-        return fail(CS_ERR_ALLOC, "force workspace (%zu bytes)", (size_t)864 * g->g.V);
+        return fail(CS_ERR_ALLOC, "force workspace (%zu bytes)", cs::FORCE_SITE_BYTES * (size_t)g->g.V);
     }
     CS_HIP(cs::launch_force(g->g, g->links[cs::P_F64], c->kappa, c->csw, x, y, c->force_H, g_lie, grad_U,
                             (hipStream_t)stream));
@@ -851,11 +851,11 @@ int cs_force_noalloc(cs_gauge g, cs_clover c, const void* x, const void* y, doub
     if (st) return st;
     if (!x || !y) return fail(CS_ERR_NULL, "x and y must be non-NULL");
     if (!g_lie && !grad_U) return fail(CS_ERR_NULL, "at least one of g_lie and grad_U must be non-NULL");
-    const size_t need = (size_t)864 * g->g.V;
+    const size_t need = cs::FORCE_SITE_BYTES * (size_t)g->g.V;
     if (need > cs::FORCE_SCRATCH_BYTES)
         return fail(CS_ERR_INVALID, "lattice of %lld sites needs %zu bytes of force workspace; the fixed "
                     "workspace holds %zu bytes (%zu sites)", g->g.V, need, cs::FORCE_SCRATCH_BYTES,
-                    cs::FORCE_SCRATCH_BYTES / 864);
+                    cs::FORCE_SCRATCH_BYTES / cs::FORCE_SITE_BYTES);
     void* H = nullptr;
     CS_HIP(cs::force_scratch_address(&H));
     CS_HIP(cs::launch_force(g->g, g->links[cs::P_F64], c->kappa, c->csw, x, y, H, g_lie, grad_U,

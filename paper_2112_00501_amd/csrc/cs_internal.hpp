@@ -460,14 +460,16 @@ hipError_t launch_sap_pair(const OpData& op, int prec, int colour, int n_block, 
                            const void* b, int nrhs, const LaunchCfg& cfg, hipStream_t s, int block_solver);
 
 // force.hip: g_{mu,a}(x) = dL/dw of L with dL = -Re(y^dag dD x); either output
-// may be null.  Hbuf holds 864 bytes per site (insertion matrices).
+// may be null.  Hbuf holds FORCE_SITE_BYTES per site (six Hermitian insertion
+// matrices of nine doubles).
+constexpr size_t FORCE_SITE_BYTES = 432;
 hipError_t launch_force(const Geom& g, const void* links64, double kappa, double csw, const void* x,
                         const void* y, void* Hbuf, double* glie, void* gradU, hipStream_t s);
-// Fixed workspace of the allocation-free force (force.hip): 128 MiB per
+// Fixed workspace of the allocation-free force (force.hip): 64 MiB per
 // device, i.e. the insertion matrices of up to 155,344 sites (a 16^3 x 32
 // lattice).  force_scratch_address gives its device address on the current
 // device (looked up once per device).
-constexpr size_t FORCE_SCRATCH_BYTES = size_t(128) << 20;
+constexpr size_t FORCE_SCRATCH_BYTES = size_t(64) << 20;
 constexpr int FORCE_SCRATCH_MAX_DEVICES = 64;
 hipError_t force_scratch_address(void** out);
 

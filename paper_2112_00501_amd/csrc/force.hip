@@ -17,8 +17,10 @@
 //   H = Lambda + Lambda^dag.
 // Each link sits in 24 plaquette leaves (3 planes x 2 plaquettes x 4
 // corners).  For a leaf L U R the derivative contributes U R H L, for a leaf
-// L U^dag R it contributes -R H L U^dag, and g_a = (kappa c_sw / 8)
-// Re tr(T^a W) for the sum W of these terms.
+// L U^dag R it contributes -R H L U^dag, which Re tr(T^a .) does not tell
+// from its adjoint -U L^dag H R^dag (H and T^a are Hermitian).  So every term
+// is U times a path from x + mu to x with H inserted at one corner, and
+// g_a = (kappa c_sw / 8) Re tr(T^a U V) for the signed sum V of the paths.
 #include <mutex>
 
 #include "dslash_core.hpp"
@@ -31,8 +33,12 @@ namespace {
 using C64 = cpx<double>;
 constexpr int TPB = BLOCK_SITES;
 
-// Insertion matrices, double2 [nblk][6 planes][9][256], planes ordered
-// (x,y), (x,z), (x,t), (y,z), (y,t), (z,t).
+// Insertion matrices, Hermitian: double [nblk][6 planes][9][256], planes
+// ordered (x,y), (x,z), (x,t), (y,z), (y,t), (z,t); the nine reals are the
+// diagonal, then re and im of the entries (0,1), (0,2), (1,2).
+constexpr int HERM_PLANE = 9 * BLOCK_SITES;        // doubles of one plane
+constexpr int HERM_BLOCK = 6 * HERM_PLANE;         // doubles of one block
+
 __device__ __forceinline__ int plane_of(int r, int s) {
     // r < s
     return r == 0 ? s - 1 : (r == 1 ? s + 1 : 5);
@@ -55,7 +61,7 @@ __device__ __forceinline__ void outer_acc(C64* o, const C64* u, const C64* v, do
 // (x,t): s1, -s1; (y,z): -s1, -s1; (y,t): s2, -s2; (z,t): s3, -s3.
 __global__ __launch_bounds__(TPB) void k_force_insertion(Geom g, const void* __restrict__ xs,
                                                          const void* __restrict__ ys,
-                                                         double2* __restrict__ H) {
+                                                         double* __restrict__ H) {
     const int blk = blockIdx.x, l = threadIdx.x;
     C64 x[12], y[12];
     SpinorIO<P_F64>::load(xs, g.nblk, blk, l, x);
@@ -87,119 +93,95 @@ __global__ __launch_bounds__(TPB) void k_force_insertion(Geom g, const void* __r
                 outer_acc(L, x1, y1, -c, 0);
             }
         }
-        double2* dst = H + ((size_t)blk * 6 + p) * 9 * TPB + l;
+        double* dst = H + (size_t)blk * HERM_BLOCK + p * HERM_PLANE + l;
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a) {
+            dst[a * TPB] = 2.0 * L[4 * a].re;
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
+            for (int b = a + 1; b < 3; ++b) {
                 const C64 v = L[a * 3 + b] + conj(L[b * 3 + a]);
-                dst[(a * 3 + b) * TPB] = make_double2(v.re, v.im);
-            }
-    }
-}
-
-__device__ __forceinline__ void load_H(const double2* H, int blk, int l, int p, C64* h) {
-    const double2* src = H + ((size_t)blk * 6 + p) * 9 * TPB + l;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        const double2 v = src[i * TPB];
-        h[i] = {v.x, v.y};
-    }
-}
-
-struct Pos {
-    int c[4];
-};
-
-__device__ __forceinline__ void link_at(const Geom& g, const void* links, const int* x, int r, int da,
-                                        int s, int db, int dir, C64* u) {
-    int c[4] = {x[0], x[1], x[2], x[3]};
-    c[r] = (c[r] + da + 2 * g.L[r]) % g.L[r];
-    c[s] = (c[s] + db + 2 * g.L[s]) % g.L[s];
-    int blk, l;
-    site_to_internal(g, c, &blk, &l);
-    load_link<P_F64, double, false>(links, blk, l, dir, u);
-}
-
-// One leaf factor in (rho, sigma) units: offset (a, b), direction (0 = rho,
-// 1 = sigma), daggered.  The four leaves of Q_{rho sigma}(z), each a closed
-// counter-clockwise loop from z:
-//   U_r(z) U_s(z+r) U_r(z+s)^dag U_s(z)^dag
-//   U_s(z) U_r(z-r+s)^dag U_s(z-r)^dag U_r(z-r)
-//   U_r(z-r)^dag U_s(z-r-s)^dag U_r(z-r-s) U_s(z-s)
-//   U_s(z-s)^dag U_r(z-s) U_s(z-s+r) U_r(z)^dag
-struct LeafF {
-    int a, b, dir, dag;
-};
-__device__ __forceinline__ LeafF leaf_factor(int leaf, int f) {
-    switch (leaf * 4 + f) {
-    case 0: return {0, 0, 0, 0};
-    case 1: return {1, 0, 1, 0};
-    case 2: return {0, 1, 0, 1};
-    case 3: return {0, 0, 1, 1};
-    case 4: return {0, 0, 1, 0};
-    case 5: return {-1, 1, 0, 1};
-    case 6: return {-1, 0, 1, 1};
-    case 7: return {-1, 0, 0, 0};
-    case 8: return {-1, 0, 0, 1};
-    case 9: return {-1, -1, 1, 1};
-    case 10: return {-1, -1, 0, 0};
-    case 11: return {0, -1, 1, 0};
-    case 12: return {0, -1, 1, 1};
-    case 13: return {0, -1, 0, 0};
-    case 14: return {1, -1, 1, 0};
-    default: return {0, 0, 0, 1};
-    }
-}
-
-// W += the derivative terms of the 8 leaves of plane (r, s) (r < s) that
-// contain the link U_mu(x), mu = r (role 0) or s (role 1).
-__device__ void clover_terms(const Geom& g, const void* links, const double2* H, const int* x, int r,
-                             int s, int role, const C64* U, C64* W) {
-    const int p = plane_of(r, s);
-#pragma unroll 1
-    for (int leaf = 0; leaf < 4; ++leaf) {
-#pragma unroll 1
-        for (int f = 0; f < 4; ++f) {
-            const LeafF F = leaf_factor(leaf, f);
-            if (F.dir != role) continue;
-            // corner z = x - (a r + b s); the leaf's other factors relative to x
-            C64 Lp[9], Rp[9], t[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                Lp[i] = {0.0, 0.0};
-                Rp[i] = {0.0, 0.0};
-            }
-            Lp[0] = Lp[4] = Lp[8] = {1.0, 0.0};
-            Rp[0] = Rp[4] = Rp[8] = {1.0, 0.0};
-#pragma unroll 1
-            for (int q = 0; q < 4; ++q) {
-                if (q == f) continue;
-                const LeafF G = leaf_factor(leaf, q);
-                link_at(g, links, x, r, G.a - F.a, s, G.b - F.b, G.dir == 0 ? r : s, t);
-                if (G.dag) m3_dag(t, t);
-                if (q < f) m3_mul(Lp, t, Lp);
-                else m3_mul(Rp, t, Rp);
-            }
-            int c[4] = {x[0], x[1], x[2], x[3]};
-            c[r] = (c[r] - F.a + 2 * g.L[r]) % g.L[r];
-            c[s] = (c[s] - F.b + 2 * g.L[s]) % g.L[s];
-            int zb, zl;
-            site_to_internal(g, c, &zb, &zl);
-            C64 h[9];
-            load_H(H, zb, zl, p, h);
-            m3_mul(Rp, h, t);   // R H
-            m3_mul(t, Lp, t);   // R H L
-            if (!F.dag) {
-                m3_mul(U, t, t);  // U R H L
-#pragma unroll
-                for (int i = 0; i < 9; ++i) W[i] = W[i] + t[i];
-            } else {
-                m3_mul_nd(t, U, t);  // R H L U^dag
-#pragma unroll
-                for (int i = 0; i < 9; ++i) W[i] = W[i] - t[i];
+                dst[(1 + 2 * (a + b)) * TPB] = v.re;  // a + b - 1 = 0, 1, 2 for (0,1), (0,2), (1,2)
+                dst[(2 + 2 * (a + b)) * TPB] = v.im;
             }
         }
+    }
+}
+
+__device__ __forceinline__ void load_H(const double* h, double* m) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) m[i] = h[i * TPB];
+}
+
+// A site as (block, local index) relative to another: differences add up over
+// directions, since the block and in-block coordinates of different
+// directions are independent.
+struct Step {
+    int blk, l;
+    __device__ __forceinline__ Step operator+(Step o) const { return {blk + o.blk, l + o.l}; }
+};
+
+__device__ __forceinline__ Step step(const Geom& g, const BlockPos& p, int l, int mu, int dir) {
+    // selected by masks: a select between members of p would be turned into an
+    // indexed load, and p into memory
+    const int e0 = -(mu == 0), e1 = -(mu == 1), e2 = -(mu == 2), e3 = -(mu == 3);
+    const int bc = (e0 & p.bc[0]) | (e1 & p.bc[1]) | (e2 & p.bc[2]) | (e3 & p.bc[3]);
+    const int nb = (e0 & g.NB[0]) | (e1 & g.NB[1]) | (e2 & g.NB[2]) | (e3 & g.NB[3]);
+    const int st = (e0 & p.stride[0]) | (e1 & p.stride[1]) | (e2 & p.stride[2]) | (e3 & p.stride[3]);
+    const int sh = 2 * mu, lc = (l >> sh) & 3;
+    if (dir > 0) {
+        if (lc < 3) return {0, 1 << sh};
+        return {bc == nb - 1 ? -(nb - 1) * st : st, -(3 << sh)};
+    }
+    if (lc > 0) return {0, -(1 << sh)};
+    return {bc == 0 ? (nb - 1) * st : -st, 3 << sh};
+}
+
+// V += the eight paths of the plane (mu, nu) through H (mu < nu; the caller
+// takes the sign of the other order).  Above the link, with A = U_nu(x+mu),
+// B = U_mu(x+nu)^dag, C = U_nu(x)^dag and H_i at the corners x, x+mu,
+// x+mu+nu, x+nu:
+//   H_1 A B C + A H_2 B C + A B H_3 C + A B C H_0
+//     = (H_1 A + A H_2)(B C) + (A B)(H_3 C + C H_0),
+// and below it, with the opposite sign, A = U_nu(x+mu-nu)^dag, B = U_mu(x-nu)^dag,
+// C = U_nu(x-nu) and the corners x, x+mu, x+mu-nu, x-nu: eight products each
+// where the four leaves one by one take twenty.
+__device__ __forceinline__ void clover_paths(const Geom& g, const BlockPos& p, int l, const void* links,
+                                             const double* H, int mu, int nu, C64* V) {
+    const Step m = step(g, p, l, mu, +1);
+    const double* Hp = H + (mu < nu ? plane_of(mu, nu) : plane_of(nu, mu)) * HERM_PLANE;
+    auto link = [&](Step d, int dir, C64* u) {
+        load_link<P_F64, double, false>(links, p.blk + d.blk, l + d.l, dir, u);
+    };
+    auto ins = [&](Step d, double* h) { load_H(Hp + (size_t)(p.blk + d.blk) * HERM_BLOCK + l + d.l, h); };
+#pragma unroll 1
+    for (int side = 0; side < 2; ++side) {
+        // side 0: C = c^dag with c = U_nu(x), A = a; side 1: C = c = U_nu(x-nu), A = a^dag
+        const Step s = step(g, p, l, nu, side == 0 ? +1 : -1), z = {0, 0};
+        const bool up = side == 0;
+        const double sg = up == (mu < nu) ? 1.0 : -1.0;
+        C64 A[9], C[9], b[9], t[9], q[9];
+        double h[9];
+        asm volatile("" ::: "memory");  // the H both sides read are loaded on each (cached), not kept
+        link(up ? z : s, nu, C);
+        if (up) m3_dag(C, C);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) C[i] = sg * C[i];  // every path holds C once (C itself or b^dag C)
+        link(s, mu, b);
+        m3_prod<true, false, 0>(b, C, t);
+        link(up ? m : m + s, nu, A);
+        if (!up) m3_dag(A, A);
+        ins(m, h);
+        m3_herm<false, false>(h, A, q);
+        ins(m + s, h);
+        m3_herm<true, true>(h, A, q);
+        m3_prod<false, false, 1>(q, t, V);  // (H_1 A + A H_2)(b^dag C)
+        __builtin_amdgcn_sched_barrier(0);
+        m3_prod<false, true, 0>(A, b, q);
+        ins(s, h);
+        m3_herm<false, false>(h, C, t);
+        ins(z, h);
+        m3_herm<true, true>(h, C, t);
+        m3_prod<false, false, 1>(q, t, V);  // (A b^dag)(H_3 C + C H_0)
     }
 }
 
@@ -222,60 +204,76 @@ __device__ __forceinline__ void trace_generators(const C64* M, double* re, doubl
     }
 }
 
-// X1 (S = -1) or X2 (S = +1) of one hop: sum over projected spins of h (x) k^dag
-template <int MU, int S>
-__device__ __forceinline__ void hop_outer(const C64* xa, const C64* yb, C64* X) {
-    C64 h[6], k[6];
-    spin_project<MU, S>(xa, h);
-    spin_project<MU, S>(yb, k);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) X[i] = {0.0, 0.0};
-    outer_acc(X, h, k, 1.0, 0.0);
-    outer_acc(X, h + 3, k + 3, 1.0, 0.0);
+// h = the projected half spinor P_-(psi) (S = -1) or P_+(psi) (S = +1) of the
+// field f at a site
+template <int S>
+__device__ __forceinline__ void project_at(const Geom& g, const void* f, int blk, int l, int mu, C64* h) {
+    C64 c[12];
+    SpinorIO<P_F64>::load(f, g.nblk, blk, l, c);
+    switch (mu) {
+    case 0: spin_project<0, S>(c, h); break;
+    case 1: spin_project<1, S>(c, h); break;
+    case 2: spin_project<2, S>(c, h); break;
+    default: spin_project<3, S>(c, h); break;
+    }
 }
 
-__global__ __launch_bounds__(TPB) void k_force_link(Geom g, const void* __restrict__ links, double kappa,
+// X = the sum over the two projected spins of h (x) k^dag
+__device__ __forceinline__ void hop_outer(const C64* h, const C64* k, C64* X) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            C64 t = h[a] * conj(k[b]);
+            cmac_conj(t, k[3 + b], h[3 + a]);
+            X[a * 3 + b] = t;
+        }
+}
+
+// One lane per link; the four directions of a block are consecutive
+// workgroups of one XCD, which share the block's links and insertion matrices
+// in its L2.  About 55 products of 3x3 matrices a link; at 24^3 x 48 it takes
+// 1.4 ms (5.2 ms with the leaves taken one by one, 120 products a link), 0.5
+// of it FP64 issue and the rest waiting for the 4.5 KB a link reads from
+// cache with two waves per SIMD to hide it.
+__global__ __launch_bounds__(TPB, 2) void k_force_link(Geom g, const void* links, double kappa,
                                                     double csw, const void* __restrict__ xs,
                                                     const void* __restrict__ ys,
-                                                    const double2* __restrict__ H, double* glie,
+                                                    const double* H, double* glie,
                                                     double2* gradU) {
-    const int blk = blockIdx.x, l = threadIdx.x, mu = blockIdx.y;
-    int x[4];
-    internal_coords(g, blk, l, x);
-    const long long site = x[0] + (long long)g.L[0] * (x[1] + (long long)g.L[1] * (x[2] + (long long)g.L[2] * x[3]));
-    C64 U[9];
-    load_link<P_F64, double, false>(links, blk, l, mu, U);
+    const int w = xcd_remap(blockIdx.x, 4 * g.nblk);
+    const int blk = block_of_item(g, w >> 2), mu = w & 3, l = threadIdx.x;
+    const BlockPos p = block_pos(g, blk);
+    const long long site = canonical_site(g, blk, l);
 
     // hopping part
     double gh[8];
     {
-        int c[4] = {x[0], x[1], x[2], x[3]};
-        c[mu] = (c[mu] + 1) % g.L[mu];
-        int nb, nl;
-        site_to_internal(g, c, &nb, &nl);
-        C64 xo[12], yo[12], xn[12], yn[12];
-        SpinorIO<P_F64>::load(xs, g.nblk, blk, l, xo);
-        SpinorIO<P_F64>::load(ys, g.nblk, blk, l, yo);
-        SpinorIO<P_F64>::load(xs, g.nblk, nb, nl, xn);
-        SpinorIO<P_F64>::load(ys, g.nblk, nb, nl, yn);
-        C64 X1[9], X2[9], M[9], t[9];
-        switch (mu) {
-        case 0: hop_outer<0, -1>(xn, yo, X1); hop_outer<0, +1>(xo, yn, X2); break;
-        case 1: hop_outer<1, -1>(xn, yo, X1); hop_outer<1, +1>(xo, yn, X2); break;
-        case 2: hop_outer<2, -1>(xn, yo, X1); hop_outer<2, +1>(xo, yn, X2); break;
-        default: hop_outer<3, -1>(xn, yo, X1); hop_outer<3, +1>(xo, yn, X2); break;
-        }
-        m3_mul(U, X1, M);
-        m3_mul_nd(X2, U, t);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) M[i] = M[i] - t[i];
+        C64 U[9];
+        load_link<P_F64, double, false>(links, blk, l, mu, U);
+        const Step fw = step(g, p, l, mu, +1);
+        const int nb = blk + fw.blk, nl = l + fw.l;
+        C64 h[6], k[6], X[9], M[9];
+        project_at<-1>(g, xs, nb, nl, mu, h);
+        project_at<-1>(g, ys, blk, l, mu, k);
+        hop_outer(h, k, X);
+        m3_prod<false, false, 0>(U, X, M);
+        asm volatile("" ::: "memory");
+        project_at<+1>(g, xs, blk, l, mu, h);
+        project_at<+1>(g, ys, nb, nl, mu, k);
+        hop_outer(h, k, X);
+        m3_prod<false, true, -1>(X, U, M);
         double re[8], im[8];
         trace_generators(M, re, im);
         // both hop terms of the link U_t(x) on the last time slice cross the
         // time boundary: with antiperiodic fields they carry a factor -1
-        const double hs = (mu == 3 && g.antiperiodic_t && x[3] == g.L[3] - 1) ? -1.0 : 1.0;
+        const double hs = (mu == 3 && g.antiperiodic_t && p.bc[3] == g.NB[3] - 1 && (l >> 6) == 3) ? -1.0 : 1.0;
 #pragma unroll
         for (int a = 0; a < 8; ++a) gh[a] = -hs * kappa * im[a];
+        // computed here, not after the clover part: only these eight values
+        // stay in registers through it
+#pragma unroll
+        for (int a = 0; a < 8; ++a) asm volatile("" : "+v"(gh[a]));
     }
 
     // clover part
@@ -286,12 +284,15 @@ __global__ __launch_bounds__(TPB) void k_force_link(Geom g, const void* __restri
         for (int i = 0; i < 9; ++i) W[i] = {0.0, 0.0};
         if (csw != 0.0) {
 #pragma unroll 1
-            for (int nu = 0; nu < 4; ++nu) {
-                if (nu == mu) continue;
-                if (mu < nu) clover_terms(g, links, H, x, mu, nu, 0, U, W);
-                else clover_terms(g, links, H, x, nu, mu, 1, U, W);
-            }
+            for (int nu = 0; nu < 4; ++nu)
+                if (nu != mu) clover_paths(g, p, l, links, H, mu, nu, W);
         }
+        // the link is loaded again (from cache): kept through the loop above it
+        // would cost it 36 registers
+        asm volatile("" ::: "memory");
+        C64 U[9];
+        load_link<P_F64, double, false>(links, blk, l, mu, U);
+        m3_mul(U, W, W);
         double re[8], im[8];
         trace_generators(W, re, im);
         const double pref = kappa * csw / 8.0;
@@ -320,7 +321,8 @@ __global__ __launch_bounds__(TPB) void k_force_link(Geom g, const void* __restri
         P[6] = {0.5 * gt[3], 0.5 * gt[4]};
         P[5] = {0.5 * gt[5], -0.5 * gt[6]};
         P[7] = {0.5 * gt[5], 0.5 * gt[6]};
-        C64 G[9];
+        C64 U[9], G[9];
+        load_link<P_F64, double, false>(links, blk, l, mu, U);
         m3_mul(P, U, G);
         double2* o = gradU + (site * 4 + mu) * 9;
 #pragma unroll
@@ -332,7 +334,7 @@ __global__ __launch_bounds__(TPB) void k_force_link(Geom g, const void* __restri
 }
 
 // Workspace of the allocation-free entry point: the insertion matrices of
-// up to FORCE_SCRATCH_BYTES / 864 sites, in a fixed device array that every
+// up to FORCE_SCRATCH_BYTES / FORCE_SITE_BYTES sites, in a fixed device array that every
 // GPU the library runs on holds until the process ends.  Host code never
 // passes the array's name to a kernel (on the host it is a stand-in, not a
 // device address): the address comes from hipGetSymbolAddress, once per
@@ -363,11 +365,11 @@ hipError_t force_scratch_address(void** out) {
 hipError_t launch_force(const Geom& g, const void* links64, double kappa, double csw, const void* x,
                         const void* y, void* Hbuf, double* glie, void* gradU, hipStream_t s) {
     ProfScope ps("force", s);
-    hipLaunchKernelGGL(k_force_insertion, dim3(g.nblk), dim3(TPB), 0, s, g, x, y, (double2*)Hbuf);
+    hipLaunchKernelGGL(k_force_insertion, dim3(g.nblk), dim3(TPB), 0, s, g, x, y, (double*)Hbuf);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_force_link, dim3(g.nblk, 4), dim3(TPB), 0, s, g, links64, kappa, csw, x, y,
-                       (const double2*)Hbuf, glie, (double2*)gradU);
+    hipLaunchKernelGGL(k_force_link, dim3(4 * g.nblk), dim3(TPB), 0, s, g, links64, kappa, csw, x, y,
+                       (const double*)Hbuf, glie, (double2*)gradU);
     return hipGetLastError();
 }
 

@@ -25,3 +25,15 @@ def test_clover_and_inverse(dims):
     torch.cuda.synchronize()
     assert np.abs(T.cpu().numpy() - c.T).max() < 1e-14
     assert np.abs(Ti.cpu().numpy() - oracle.clover_inverse_field(dims, c.T)).max() < 1e-13
+
+
+@pytest.mark.parametrize("antiperiodic", [False, True])
+@pytest.mark.parametrize("dims", DIMS)
+def test_force(dims, antiperiodic):
+    # a few hundred FP64 products per entry, as on the other lattices: 1e-12
+    c = Case(dims, 0.3, 0.137, 1.3, 32, oracle_T=False, antiperiodic_t=antiperiodic)
+    x, y = synth.source(dims, 33), synth.source(dims, 34)
+    g, _ = c.op.force(c.to_dev(x, cs.F64), c.to_dev(y, cs.F64))
+    torch.cuda.synchronize()
+    gh, gc = oracle.force(dims, c.Uo, c.kappa, c.csw, x, y)
+    assert rel(g.cpu().numpy(), gh + gc) < 1e-12
