@@ -18,6 +18,7 @@
 #include "../../include/cloversap.h"
 #include "blas.hpp"
 #include "bicgstab.hpp"
+#include "devmem.hpp"
 #include "gcr.hpp"
 #include "mg.hpp"
 #include "probe.hpp"
@@ -212,11 +213,14 @@ int cs_lattice_create(const int dims[4], const int block[4], int flags, cs_latti
     g.V = V;
     g.nblk = (int)(V / cs::BLOCK_SITES);
     *out = new cs_lattice_s{g};
+    cs::dev_lattice_created();
     return ok();
 }
 
 int cs_lattice_destroy(cs_lattice lat) {
+    if (!lat) return ok();
     delete lat;
+    cs::dev_lattice_destroyed();
     return ok();
 }
 
@@ -248,7 +252,7 @@ int cs_gauge_create(cs_lattice lat, const void* U, void* stream, cs_gauge* out) 
     auto* g = new cs_gauge_s;
     g->g = lat->g;
     for (int p = 0; p < 4; ++p) {
-        if (hipMalloc(&g->links[p], cs::link_bytes_per_site(p) * g->g.V) != hipSuccess) {
+        if (cs::dev_alloc(&g->links[p], cs::link_bytes_per_site(p) * g->g.V) != hipSuccess) {
             cs_gauge_destroy(g);
             return fail(CS_ERR_ALLOC, "could not allocate %zu bytes of links",
                         cs::link_bytes_per_site(p) * (size_t)g->g.V);
@@ -268,7 +272,7 @@ int cs_gauge_create(cs_lattice lat, const void* U, void* stream, cs_gauge* out) 
 int cs_gauge_destroy(cs_gauge g) {
     if (!g) return ok();
     for (int p = 0; p < 4; ++p)
-        if (g->links[p]) hipFree(g->links[p]);
+        if (g->links[p]) cs::dev_free(g->links[p]);
     delete g;
     return ok();
 }
@@ -280,10 +284,10 @@ int cs_clover_create(cs_gauge g, double kappa, double csw, void* stream, cs_clov
     c->gauge = g;
     c->kappa = kappa;
     c->csw = csw;
-    if (hipMalloc(&c->c64, cs::clover_bytes_per_site(cs::P_F64) * g->g.V) != hipSuccess ||
-        hipMalloc(&c->c32, cs::clover_bytes_per_site(cs::P_F32) * g->g.V) != hipSuccess ||
-        hipMalloc(&c->ci64, cs::clover_bytes_per_site(cs::P_F64) * g->g.V) != hipSuccess ||
-        hipMalloc(&c->ci32, cs::clover_bytes_per_site(cs::P_F32) * g->g.V) != hipSuccess) {
+    if (cs::dev_alloc(&c->c64, cs::clover_bytes_per_site(cs::P_F64) * g->g.V) != hipSuccess ||
+        cs::dev_alloc(&c->c32, cs::clover_bytes_per_site(cs::P_F32) * g->g.V) != hipSuccess ||
+        cs::dev_alloc(&c->ci64, cs::clover_bytes_per_site(cs::P_F64) * g->g.V) != hipSuccess ||
+        cs::dev_alloc(&c->ci32, cs::clover_bytes_per_site(cs::P_F32) * g->g.V) != hipSuccess) {
         cs_clover_destroy(c);
         return fail(CS_ERR_ALLOC, "could not allocate the clover term");
     }
@@ -303,12 +307,12 @@ int cs_clover_destroy(cs_clover c) {
     if (!c) return ok();
     c->work.reset();
     c->group_work.clear();
-    if (c->force_H) hipFree(c->force_H);
-    if (c->dag_tmp) hipFree(c->dag_tmp);
-    if (c->c64) hipFree(c->c64);
-    if (c->c32) hipFree(c->c32);
-    if (c->ci64) hipFree(c->ci64);
-    if (c->ci32) hipFree(c->ci32);
+    if (c->force_H) cs::dev_free(c->force_H);
+    if (c->dag_tmp) cs::dev_free(c->dag_tmp);
+    if (c->c64) cs::dev_free(c->c64);
+    if (c->c32) cs::dev_free(c->c32);
+    if (c->ci64) cs::dev_free(c->ci64);
+    if (c->ci32) cs::dev_free(c->ci32);
     delete c;
     return ok();
 }
@@ -432,8 +436,8 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
     const cs::OpData op = make_op(g, c);
     const size_t bytes = cs::spinor_bytes_per_site(prec) * (size_t)g->g.V * nrhs;
     void *xb = nullptr, *bb = nullptr;
-    if (hipMalloc(&xb, bytes) != hipSuccess || hipMalloc(&bb, bytes) != hipSuccess) {
-        if (xb) hipFree(xb);
+    if (cs::dev_alloc(&xb, bytes) != hipSuccess || cs::dev_alloc(&bb, bytes) != hipSuccess) {
+        if (xb) cs::dev_free(xb);
         return fail(CS_ERR_ALLOC, "autotune scratch (%zu bytes)", 2 * bytes);
     }
     int cus = 256;
@@ -488,8 +492,8 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
-    hipFree(xb);
-    hipFree(bb);
+    cs::dev_free(xb);
+    cs::dev_free(bb);
     if (err != hipSuccess) return fail(CS_ERR_HIP, "autotune: %s", hipGetErrorString(err));
     c->tuned[key] = std::make_pair(bs, bd);
     *best_sap = bs;
@@ -560,10 +564,10 @@ static int gcr_common(cs_gauge g, cs_clover c, const cs_solver_params* p, void* 
     if (overlap(b, x, f64 * nrhs)) return fail(CS_ERR_INVALID, "x and b overlap");
     hipStream_t s = (hipStream_t)stream;
     if (dagger && c->dag_tmp_nrhs < nrhs) {
-        if (c->dag_tmp) hipFree(c->dag_tmp);
+        if (c->dag_tmp) cs::dev_free(c->dag_tmp);
         c->dag_tmp = nullptr;
         c->dag_tmp_nrhs = 0;
-        if (hipMalloc(&c->dag_tmp, f64 * nrhs) != hipSuccess) {
+        if (cs::dev_alloc(&c->dag_tmp, f64 * nrhs) != hipSuccess) {
             c->dag_tmp = nullptr;
             return fail(CS_ERR_ALLOC, "adjoint-solve workspace");
         }
@@ -836,7 +840,7 @@ int cs_force(cs_gauge g, cs_clover c, const void* x, const void* y, double* g_li
     if (st) return st;
     if (!x || !y) return fail(CS_ERR_NULL, "x and y must be non-NULL");
     if (!g_lie && !grad_U) return fail(CS_ERR_NULL, "at least one of g_lie and grad_U must be non-NULL");
-    if (!c->force_H && hipMalloc(&c->force_H, cs::FORCE_SITE_BYTES * (size_t)g->g.V) != hipSuccess) {
+    if (!c->force_H && cs::dev_alloc(&c->force_H, cs::FORCE_SITE_BYTES * (size_t)g->g.V) != hipSuccess) {
         c->force_H = nullptr;
         return fail(CS_ERR_ALLOC, "force workspace (%zu bytes)", cs::FORCE_SITE_BYTES * (size_t)g->g.V);
     }

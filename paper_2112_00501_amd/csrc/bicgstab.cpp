@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "bicgstab.hpp"
+#include "devmem.hpp"
 
 namespace cs {
 
@@ -59,11 +60,11 @@ void BicgWork::drop_graph() {
 void BicgWork::release() {
     drop_graph();
     for (void** q : {&r, &rh, &p, &v, &s, &t, &plo, &slo, &zp, &zs, &w, &r64, &bin, &e}) {
-        if (*q) hipFree(*q);
+        if (*q) dev_free(*q);
         *q = nullptr;
     }
-    if (partials) hipFree(partials);
-    if (sc) hipFree(sc);
+    if (partials) dev_free(partials);
+    if (sc) dev_free(sc);
     if (host_tail) hipHostFree(host_tail);
     if (stream) hipStreamDestroy(stream);
     partials = nullptr;
@@ -88,16 +89,16 @@ hipError_t BicgWork::ensure(const Geom& g, int inner_, int pv_) {
     hipError_t err;
 #define E_(x)                                   \
     if ((err = (x)) != hipSuccess) return err
-    for (void** q : {&r, &rh, &p, &v, &s, &t}) E_(hipMalloc(q, vec));
-    for (void** q : {&plo, &slo, &zp, &zs}) E_(hipMalloc(q, lo));
-    E_(hipMalloc(&w, nat));
+    for (void** q : {&r, &rh, &p, &v, &s, &t}) E_(dev_alloc(q, vec));
+    for (void** q : {&plo, &slo, &zp, &zs}) E_(dev_alloc(q, lo));
+    E_(dev_alloc(&w, nat));
     if (pv != P_F64) {
-        E_(hipMalloc(&r64, f64));
-        E_(hipMalloc(&bin, vec));
-        E_(hipMalloc(&e, vec));
+        E_(dev_alloc(&r64, f64));
+        E_(dev_alloc(&bin, vec));
+        E_(dev_alloc(&e, vec));
     }
-    E_(hipMalloc((void**)&partials, sizeof(double2) * BLAS_MAX_WG * (MULTIDOT_CHUNK + 2)));
-    E_(hipMalloc((void**)&sc, sizeof(BiScalars)));
+    E_(dev_alloc((void**)&partials, sizeof(double2) * BLAS_MAX_WG * (MULTIDOT_CHUNK + 2)));
+    E_(dev_alloc((void**)&sc, sizeof(BiScalars)));
     // coherent: the finalize kernels write it and the host reads it after a stream wait
     E_(hipHostMalloc((void**)&host_tail, sizeof(BiTail), hipHostMallocCoherent));
     E_(hipStreamCreateWithFlags(&stream, hipStreamNonBlocking));

@@ -35,6 +35,7 @@
 #include <vector>
 
 #include "blas.hpp"
+#include "devmem.hpp"
 #include "gcr.hpp"
 
 namespace cs {
@@ -62,13 +63,13 @@ void GcrWork::drop_graphs() {
 void GcrWork::release() {
     drop_graphs();
     for (void** p : {&r, &rlo, &Z, &W, &wtmp}) {
-        if (*p) hipFree(*p);
+        if (*p) dev_free(*p);
         *p = nullptr;
     }
-    if (partials) hipFree(partials);
-    if (sc) hipFree(sc);
-    if (tail) hipFree(tail);
-    if (active) hipFree(active);
+    if (partials) dev_free(partials);
+    if (sc) dev_free(sc);
+    if (tail) dev_free(tail);
+    if (active) dev_free(active);
     if (host_ku) hipHostFree(host_ku);
     if (host_tail) hipHostFree(host_tail);
     if (host_active) hipHostFree(host_active);
@@ -100,18 +101,18 @@ hipError_t GcrWork::ensure(const Geom& g, int m_, int inner_, int basis_, int nr
     zstride = spinor_bytes_per_site(inner) * g.V;
     wstride = spinor_bytes_per_site(basis) * g.V;
     hipError_t e;
-    if ((e = hipMalloc(&r, f64 * nrhs)) != hipSuccess) return e;
-    if ((e = hipMalloc(&rlo, zstride * nrhs)) != hipSuccess) return e;
-    if ((e = hipMalloc(&Z, zstride * m * nrhs)) != hipSuccess) return e;
-    if ((e = hipMalloc(&W, wstride * m * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc(&r, f64 * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc(&rlo, zstride * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc(&Z, zstride * m * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc(&W, wstride * m * nrhs)) != hipSuccess) return e;
     if (natural_out(inner) != basis && basis != P_F16 && basis != P_BF16) {
-        if ((e = hipMalloc(&wtmp, spinor_bytes_per_site(natural_out(inner)) * g.V * nrhs)) != hipSuccess) return e;
+        if ((e = dev_alloc(&wtmp, spinor_bytes_per_site(natural_out(inner)) * g.V * nrhs)) != hipSuccess) return e;
     }
-    if ((e = hipMalloc((void**)&partials, sizeof(double2) * BLAS_MAX_WG * (MULTIDOT_CHUNK + 2) * nrhs)) != hipSuccess)
+    if ((e = dev_alloc((void**)&partials, sizeof(double2) * BLAS_MAX_WG * (MULTIDOT_CHUNK + 2) * nrhs)) != hipSuccess)
         return e;
-    if ((e = hipMalloc((void**)&sc, sizeof(GcrScalars) * nrhs)) != hipSuccess) return e;
-    if ((e = hipMalloc((void**)&tail, sizeof(GcrTail) * nrhs)) != hipSuccess) return e;
-    if ((e = hipMalloc((void**)&active, sizeof(int) * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc((void**)&sc, sizeof(GcrScalars) * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc((void**)&tail, sizeof(GcrTail) * nrhs)) != hipSuccess) return e;
+    if ((e = dev_alloc((void**)&active, sizeof(int) * nrhs)) != hipSuccess) return e;
     // coherent host memory for what kernels read or write directly: no device
     // cache holds a stale copy across solves
     if ((e = hipHostMalloc((void**)&host_ku, sizeof(int) * nrhs, hipHostMallocCoherent)) != hipSuccess) return e;

@@ -17,6 +17,7 @@
 #include <atomic>
 
 #include "blas.hpp"
+#include "devmem.hpp"
 #include "mg.hpp"
 
 namespace cs {
@@ -68,7 +69,7 @@ void MgData::drop_graphs() const {
 void MgData::release() {
     drop_graphs();
     for (void** q : {&P, &P16, &V, &tmp, (void**)&Dc, &Dc16, (void**)&rc, (void**)&cv.x, (void**)&sc, (void**)&pa.A}) {
-        if (*q) hipFree(*q);
+        if (*q) dev_free(*q);
         *q = nullptr;
     }
     if (host_flag) hipHostFree(host_flag);
@@ -83,16 +84,16 @@ hipError_t MgData::alloc(const Geom& g_, const MgParams& p_) {
     g = g_;
     p = p_;
     id = next_id++;
-    MG_CHK(hipMalloc(&P, field_bytes() * p.nv));
-    if (p.transfer_half) MG_CHK(hipMalloc(&P16, spinor_bytes_per_site(P_F16) * g.V * p.nv));
-    MG_CHK(hipMalloc(&V, field_bytes() * p.nv));
-    MG_CHK(hipMalloc(&tmp, field_bytes()));
-    MG_CHK(hipMalloc((void**)&Dc, dc_bytes()));
-    if (p.coarse_half) MG_CHK(hipMalloc(&Dc16, dc_bytes() / 2));
-    MG_CHK(hipMalloc((void**)&rc, coarse_bytes()));
+    MG_CHK(dev_alloc(&P, field_bytes() * p.nv));
+    if (p.transfer_half) MG_CHK(dev_alloc(&P16, spinor_bytes_per_site(P_F16) * g.V * p.nv));
+    MG_CHK(dev_alloc(&V, field_bytes() * p.nv));
+    MG_CHK(dev_alloc(&tmp, field_bytes()));
+    MG_CHK(dev_alloc((void**)&Dc, dc_bytes()));
+    if (p.coarse_half) MG_CHK(dev_alloc(&Dc16, dc_bytes() / 2));
+    MG_CHK(dev_alloc((void**)&rc, coarse_bytes()));
     // the nine coarse vectors and tau (4 vectors) in one allocation (cv.x owns it)
     float2* base = nullptr;
-    MG_CHK(hipMalloc((void**)&base, coarse_bytes() * 13));
+    MG_CHK(dev_alloc((void**)&base, coarse_bytes() * 13));
     const size_t n = (size_t)g.nblk * nc();
     cv.x = base;
     cv.r = base + n;
@@ -104,11 +105,11 @@ hipError_t MgData::alloc(const Geom& g_, const MgParams& p_) {
     cv.s = base + 7 * n;
     cv.t = base + 8 * n;
     cv.tau = base + 9 * n;
-    MG_CHK(hipMalloc((void**)&sc, sizeof(CbScalars)));
+    MG_CHK(dev_alloc((void**)&sc, sizeof(CbScalars)));
     // partial sums, two complex values per workgroup (pa.A owns the allocation)
     const size_t na = 2 * (size_t)MG_ELEM_WG;
     double2* pb = nullptr;
-    MG_CHK(hipMalloc((void**)&pb, sizeof(double2) * 3 * na));
+    MG_CHK(dev_alloc((void**)&pb, sizeof(double2) * 3 * na));
     pa = CbPartials{pb, pb + na, pb + 2 * na};
     MG_CHK(hipHostMalloc((void**)&host_flag, sizeof(int), hipHostMallocDefault));
     return hipSuccess;
@@ -161,16 +162,16 @@ hipError_t mg_setup(const OpData& op, MgData& m, const void* etas, hipStream_t s
     void* W = nullptr;
     float2* cvs = nullptr;
     const size_t n = (size_t)m.g.nblk * m.nc();
-    hipError_t e = hipMalloc(&W, m.field_bytes() * m.p.nv);
-    if (e == hipSuccess) e = hipMalloc((void**)&cvs, 2 * n * m.p.nv * sizeof(float2));
+    hipError_t e = dev_alloc(&W, m.field_bytes() * m.p.nv);
+    if (e == hipSuccess) e = dev_alloc((void**)&cvs, 2 * n * m.p.nv * sizeof(float2));
     for (int pass = 0; e == hipSuccess && pass < m.p.n_adapt; ++pass) {
         e = adaptive_pass(op, m, W, cvs, cvs + n * m.p.nv, s);
         if (e == hipSuccess) e = rebuild(op, m, s);
     }
     // the frees wait for the queued work that uses the workspace
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (W) hipFree(W);
-    if (cvs) hipFree(cvs);
+    if (W) dev_free(W);
+    if (cvs) dev_free(cvs);
     return e;
 }
 
