@@ -72,8 +72,8 @@ void MgData::release() {
         if (*q) dev_free(*q);
         *q = nullptr;
     }
-    if (host_flag) hipHostFree(host_flag);
-    host_flag = nullptr;
+    if (host_sc) hipHostFree(host_sc);
+    host_sc = nullptr;
     cv = CbVecs{};
     pa = CbPartials{};
 }
@@ -93,63 +93,68 @@ hipError_t MgData::alloc(const Geom& g_, const MgParams& p_) {
     MG_CHK(dev_alloc((void**)&rc, coarse_bytes()));
     // the nine coarse vectors and tau (4 vectors) in one allocation (cv.x owns it)
     float2* base = nullptr;
-    MG_CHK(dev_alloc((void**)&base, coarse_bytes() * 13));
-    const size_t n = (size_t)g.nblk * nc();
-    cv.x = base;
-    cv.r = base + n;
-    cv.rh = base + 2 * n;
-    cv.p[0] = base + 3 * n;
-    cv.p[1] = base + 4 * n;
-    cv.v[0] = base + 5 * n;
-    cv.v[1] = base + 6 * n;
-    cv.s = base + 7 * n;
-    cv.t = base + 8 * n;
-    cv.tau = base + 9 * n;
+    MG_CHK(dev_alloc((void**)&base, coarse_bytes() * CB_VECS));
+    cv.place(base, (size_t)g.nblk * nc());
     MG_CHK(dev_alloc((void**)&sc, sizeof(CbScalars)));
     // partial sums, two complex values per workgroup (pa.A owns the allocation)
-    const size_t na = 2 * (size_t)MG_ELEM_WG;
     double2* pb = nullptr;
-    MG_CHK(dev_alloc((void**)&pb, sizeof(double2) * 3 * na));
-    pa = CbPartials{pb, pb + na, pb + 2 * na};
-    MG_CHK(hipHostMalloc((void**)&host_flag, sizeof(int), hipHostMallocDefault));
+    MG_CHK(dev_alloc((void**)&pb, sizeof(double2) * 3 * CB_PARTIALS));
+    pa = CbPartials{pb, pb + CB_PARTIALS, pb + 2 * CB_PARTIALS};
+    MG_CHK(hipHostMalloc((void**)&host_sc, sizeof(CbScalars) * p.nv, hipHostMallocDefault));
     return hipSuccess;
 }
 
 namespace {
 
-// e_c = coarse BiCGStab on D_c from a given coarse right-hand side rc, left
-// in cv.x; MG_CHUNK iterations between host reads of the stop flag
-hipError_t coarse_solve_from(const MgData& m, const float2* rc, hipStream_t s) {
-    const int cap = m.p.n_coarse;
-    int done = cap < MG_CHUNK ? cap : MG_CHUNK;
-    MG_CHK(mg_coarse_begin(m.g, m.nc(), rc, m.cv, m.sc, m.pa, m.p.tol_coarse, s));
-    MG_CHK(mg_coarse_iters(m.g, m.coarse(), m.nc(), m.cv, m.sc, m.pa, 0, done, s));
-    while (done < cap) {
-        MG_CHK(hipMemcpyAsync(m.host_flag, &m.sc->stopped[done & 1], sizeof(int), hipMemcpyDeviceToHost, s));
-        MG_CHK(hipStreamSynchronize(s));
-        if (*m.host_flag) break;
-        const int to = done + MG_CHUNK < cap ? done + MG_CHUNK : cap;
-        MG_CHK(mg_coarse_iters(m.g, m.coarse(), m.nc(), m.cv, m.sc, m.pa, done, to, s));
-        done = to;
+// Workspace of the adaptive passes: nv FP32 fields, and per null vector the
+// coarse right-hand side, the coarse vectors, scalars and partial sums.
+struct PassWork {
+    void* W = nullptr;
+    float2 *rcs = nullptr, *vecs = nullptr;
+    CbScalars* sc = nullptr;
+    double2* part = nullptr;
+    hipError_t alloc(const MgData& m) {
+        const size_t nv = m.p.nv;
+        MG_CHK(dev_alloc(&W, m.field_bytes() * nv));
+        MG_CHK(dev_alloc((void**)&rcs, m.coarse_bytes() * nv));
+        MG_CHK(dev_alloc((void**)&vecs, m.coarse_bytes() * CB_VECS * nv));
+        MG_CHK(dev_alloc((void**)&sc, sizeof(CbScalars) * nv));
+        return dev_alloc((void**)&part, sizeof(double2) * 3 * CB_PARTIALS * nv);
     }
-    return hipSuccess;
-}
+    ~PassWork() {
+        for (void* q : {W, (void*)rcs, (void*)vecs, (void*)sc, (void*)part}) dev_free(q);
+    }
+};
 
 // One adaptive pass, v_i <- M_MG v_i for all null vectors at once: one
-// restriction of all of them, the coarse solves one after another, one
+// restriction of all of them, the coarse solves of all of them side by side
+// (one launch per step of the solver, D_c read once for four), one
 // prolongation of all, and the post-smoothing as one batched SAP launch per
 // half-sweep (the results are those of M_MG applied to each v_i in turn).
-// W: nv FP32 fields, rcs and ecs: nv coarse vectors each.
-hipError_t adaptive_pass(const OpData& op, MgData& m, void* W, float2* rcs, float2* ecs, hipStream_t s) {
+// The coarse iterations run in chunks until the host sees every solve stopped.
+hipError_t adaptive_pass(const OpData& op, MgData& m, const PassWork& w, hipStream_t s) {
+    const int nv = m.p.nv, cap = m.p.n_coarse;
     const size_t n = (size_t)m.g.nblk * m.nc();
-    MG_CHK(mg_restrict_many(m.g, m.transfer(), m.p.nv, m.V, m.p.nv, rcs, s));
-    for (int i = 0; i < m.p.nv; ++i) {
-        MG_CHK(coarse_solve_from(m, rcs + (size_t)i * n, s));
-        MG_CHK(hipMemcpyAsync(ecs + (size_t)i * n, m.cv.x, n * sizeof(float2), hipMemcpyDeviceToDevice, s));
+    MG_CHK(mg_restrict_many(m.g, m.transfer(), nv, m.V, nv, w.rcs, s));
+    CbVecs cv;
+    cv.place(w.vecs, n);
+    const CbPartials pa{w.part, w.part + CB_PARTIALS * nv, w.part + 2 * CB_PARTIALS * nv};
+    int done = cap < MG_CHUNK ? cap : MG_CHUNK;
+    MG_CHK(mg_coarse_begin(m.g, m.nc(), nv, w.rcs, cv, w.sc, pa, m.p.tol_coarse, s));
+    MG_CHK(mg_coarse_iters(m.g, m.coarse(), m.nc(), nv, cv, w.sc, pa, 0, done, s));
+    while (done < cap) {
+        MG_CHK(hipMemcpyAsync(m.host_sc, w.sc, sizeof(CbScalars) * nv, hipMemcpyDeviceToHost, s));
+        MG_CHK(hipStreamSynchronize(s));
+        bool all = true;
+        for (int i = 0; i < nv; ++i) all = all && m.host_sc[i].stopped[done & 1];
+        if (all) break;
+        const int to = done + MG_CHUNK < cap ? done + MG_CHUNK : cap;
+        MG_CHK(mg_coarse_iters(m.g, m.coarse(), m.nc(), nv, cv, w.sc, pa, done, to, s));
+        done = to;
     }
-    MG_CHK(mg_prolong_many(m.g, m.transfer(), m.p.nv, ecs, m.p.nv, W, s));
-    MG_CHK(sap_cycles(op, m.sap_cfg, m.p.n_cy_post, m.p.n_mr, false, W, m.V, m.p.nv, s));
-    return hipMemcpyAsync(m.V, W, m.field_bytes() * m.p.nv, hipMemcpyDeviceToDevice, s);
+    MG_CHK(mg_prolong_many(m.g, m.transfer(), nv, cv.x, cv.rs, nv, w.W, s));
+    MG_CHK(sap_cycles(op, m.sap_cfg, m.p.n_cy_post, m.p.n_mr, false, w.W, m.V, nv, s));
+    return hipMemcpyAsync(m.V, w.W, m.field_bytes() * nv, hipMemcpyDeviceToDevice, s);
 }
 
 }  // namespace
@@ -158,21 +163,14 @@ hipError_t mg_setup(const OpData& op, MgData& m, const void* etas, hipStream_t s
     MG_CHK(sap_cycles(op, m.sap_cfg, m.p.n_cy_setup, m.p.n_mr, true, m.V, etas, m.p.nv, s));
     MG_CHK(rebuild(op, m, s));
     if (m.p.n_adapt <= 0) return hipSuccess;
-    // workspace of the batched passes, released once the passes are done
-    void* W = nullptr;
-    float2* cvs = nullptr;
-    const size_t n = (size_t)m.g.nblk * m.nc();
-    hipError_t e = dev_alloc(&W, m.field_bytes() * m.p.nv);
-    if (e == hipSuccess) e = dev_alloc((void**)&cvs, 2 * n * m.p.nv * sizeof(float2));
-    for (int pass = 0; e == hipSuccess && pass < m.p.n_adapt; ++pass) {
-        e = adaptive_pass(op, m, W, cvs, cvs + n * m.p.nv, s);
-        if (e == hipSuccess) e = rebuild(op, m, s);
+    // the workspace of the batched passes is given back once they are done
+    PassWork w;
+    MG_CHK(w.alloc(m));
+    for (int pass = 0; pass < m.p.n_adapt; ++pass) {
+        MG_CHK(adaptive_pass(op, m, w, s));
+        MG_CHK(rebuild(op, m, s));
     }
-    // the frees wait for the queued work that uses the workspace
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (W) dev_free(W);
-    if (cvs) dev_free(cvs);
-    return e;
+    return hipStreamSynchronize(s);
 }
 
 namespace {
@@ -215,18 +213,19 @@ hipError_t mg_coarse_phase(const MgData& m, const void* r, hipStream_t s, bool u
     int done = cap < MG_CHUNK ? cap : MG_CHUNK;
     MG_CHK(run_piece(&G.first, use_graph, s, [&]() -> hipError_t {
         MG_CHK(mg_restrict(m.g, m.transfer(), m.p.nv, r, m.rc, s));
-        MG_CHK(mg_coarse_begin(m.g, m.nc(), m.rc, m.cv, m.sc, m.pa, m.p.tol_coarse, s));
-        return mg_coarse_iters(m.g, m.coarse(), m.nc(), m.cv, m.sc, m.pa, 0, done, s);
+        MG_CHK(mg_coarse_begin(m.g, m.nc(), 1, m.rc, m.cv, m.sc, m.pa, m.p.tol_coarse, s));
+        return mg_coarse_iters(m.g, m.coarse(), m.nc(), 1, m.cv, m.sc, m.pa, 0, done, s);
     }));
     for (int j = 0; done < cap; ++j) {
         // stopped[done & 1] was set by the stop test of iteration `done`
-        MG_CHK(hipMemcpyAsync(m.host_flag, &m.sc->stopped[done & 1], sizeof(int), hipMemcpyDeviceToHost, s));
+        MG_CHK(hipMemcpyAsync(&m.host_sc->stopped[done & 1], &m.sc->stopped[done & 1], sizeof(int),
+                              hipMemcpyDeviceToHost, s));
         MG_CHK(hipStreamSynchronize(s));
-        if (*m.host_flag) break;
+        if (m.host_sc->stopped[done & 1]) break;
         const int to = done + MG_CHUNK < cap ? done + MG_CHUNK : cap;
         if ((int)G.chunk.size() <= j) G.chunk.resize(j + 1, nullptr);
         MG_CHK(run_piece(&G.chunk[j], use_graph, s, [&]() -> hipError_t {
-            return mg_coarse_iters(m.g, m.coarse(), m.nc(), m.cv, m.sc, m.pa, done, to, s);
+            return mg_coarse_iters(m.g, m.coarse(), m.nc(), 1, m.cv, m.sc, m.pa, done, to, s);
         }));
         done = to;
     }

@@ -48,9 +48,12 @@ __device__ __forceinline__ void load_f32(const char* P, size_t fs, int i, int nb
 
 // Block index one step in direction mu (dir = +1 / -1) with periodic wrap.
 __device__ __forceinline__ int block_step(const Geom& g, const BlockPos& p, int mu, int dir) {
-    const int bc = mu == 0 ? p.bc[0] : mu == 1 ? p.bc[1] : mu == 2 ? p.bc[2] : p.bc[3];
-    const int nb = mu == 0 ? g.NB[0] : mu == 1 ? g.NB[1] : mu == 2 ? g.NB[2] : g.NB[3];
-    const int st = mu == 0 ? p.stride[0] : mu == 1 ? p.stride[1] : mu == 2 ? p.stride[2] : p.stride[3];
+    // selected by masks: a select between members of p would be turned into an
+    // indexed load, and p into memory
+    const int e0 = -(mu == 0), e1 = -(mu == 1), e2 = -(mu == 2), e3 = -(mu == 3);
+    const int bc = (e0 & p.bc[0]) | (e1 & p.bc[1]) | (e2 & p.bc[2]) | (e3 & p.bc[3]);
+    const int nb = (e0 & g.NB[0]) | (e1 & g.NB[1]) | (e2 & g.NB[2]) | (e3 & g.NB[3]);
+    const int st = (e0 & p.stride[0]) | (e1 & p.stride[1]) | (e2 & p.stride[2]) | (e3 & p.stride[3]);
     if (dir > 0) return bc == nb - 1 ? p.blk - (nb - 1) * st : p.blk + st;
     return bc == 0 ? p.blk + (nb - 1) * st : p.blk - st;
 }
@@ -426,63 +429,84 @@ __device__ __forceinline__ float2 cm_load(const void* M, size_t i) {
     return ((const float2*)M)[i];
 }
 
-// y_row = sum over the self and -mu blocks of aggregate a of M[k][row] xs[k];
-// valid in lanes t < nc (others return 0)
-template <bool HALF>
-__device__ __forceinline__ float2 cmv_rows5(const void* __restrict__ Dc, int a, int nc, const float2* xs,
-                                            float2* red) {
+// R right-hand sides share one pass over the matrices: xs[j], y[j] and
+// tau + j * rs are those of right-hand side j, each with the sums it has alone.
+
+// y[j]_row = sum over the self and -mu blocks of aggregate a of M[k][row]
+// xs[j][k]; valid in lanes t < nc
+template <bool HALF, int R>
+__device__ __forceinline__ void cmv_rows5(const void* __restrict__ Dc, int a, int nc, const float2 (*xs)[CMV_KMAX],
+                                          float2* red, float2* y) {
     const int t = threadIdx.x, kch = CMV_TPB / nc, row = t % nc, kc = t / nc, K5 = 5 * nc;
     const size_t base = (size_t)a * 9 * nc * nc + row;
-    float re = 0.f, im = 0.f, re2 = 0.f, im2 = 0.f;
+    float re[R], im[R], re2[R], im2[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) re[j] = im[j] = re2[j] = im2[j] = 0.f;
+    auto mac = [](float2 m, float2 x, float& re_, float& im_) {
+        re_ = fmaf(m.x, x.x, re_);
+        re_ = fmaf(-m.y, x.y, re_);
+        im_ = fmaf(m.x, x.y, im_);
+        im_ = fmaf(m.y, x.x, im_);
+    };
     if (kc < kch) {
         int k = kc;
         for (; k + kch < K5; k += 2 * kch) {
             const int k1 = k + kch;
             const float2 m0 = cm_load<HALF>(Dc, base + (size_t)(slot_dir(k / nc) * nc + k % nc) * nc);
             const float2 m1 = cm_load<HALF>(Dc, base + (size_t)(slot_dir(k1 / nc) * nc + k1 % nc) * nc);
-            const float2 x0 = xs[k], x1 = xs[k1];
-            re = fmaf(m0.x, x0.x, re); re = fmaf(-m0.y, x0.y, re);
-            im = fmaf(m0.x, x0.y, im); im = fmaf(m0.y, x0.x, im);
-            re2 = fmaf(m1.x, x1.x, re2); re2 = fmaf(-m1.y, x1.y, re2);
-            im2 = fmaf(m1.x, x1.y, im2); im2 = fmaf(m1.y, x1.x, im2);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                mac(m0, xs[j][k], re[j], im[j]);
+                mac(m1, xs[j][k1], re2[j], im2[j]);
+            }
         }
         if (k < K5) {
-            const float2 m0 = cm_load<HALF>(Dc, base + (size_t)(slot_dir(k / nc) * nc + k % nc) * nc), x0 = xs[k];
-            re = fmaf(m0.x, x0.x, re); re = fmaf(-m0.y, x0.y, re);
-            im = fmaf(m0.x, x0.y, im); im = fmaf(m0.y, x0.x, im);
+            const float2 m0 = cm_load<HALF>(Dc, base + (size_t)(slot_dir(k / nc) * nc + k % nc) * nc);
+#pragma unroll
+            for (int j = 0; j < R; ++j) mac(m0, xs[j][k], re[j], im[j]);
         }
     }
-    red[t] = make_float2(re + re2, im + im2);
-    __syncthreads();
-    float2 y = make_float2(0.f, 0.f);
-    if (t < nc)
-        for (int c = 0; c < kch; ++c) {
-            const float2 v = red[c * nc + t];
-            y.x += v.x;
-            y.y += v.y;
-        }
-    return y;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if (j > 0) __syncthreads();  // the previous right-hand side's readers of red are done
+        red[t] = make_float2(re[j] + re2[j], im[j] + im2[j]);
+        __syncthreads();
+        y[j] = make_float2(0.f, 0.f);
+        if (t < nc)
+            for (int c = 0; c < kch; ++c) {
+                const float2 v = red[c * nc + t];
+                y[j].x += v.x;
+                y[j].y += v.y;
+            }
+    }
 }
 
 // tau[a][mu][i] = sum_c g5(i) g5(c) conj(D_c[a][-mu][col i][row c]) xa[c],
-// xa the aggregate's own entries (LDS)
-template <bool HALF>
-__device__ __forceinline__ void cmv_adjoint4(const void* __restrict__ Dc, int a, int nc, const float2* xa,
-                                             float2* __restrict__ tau) {
+// xa the aggregate's own entries (LDS); written where bit j of live is set
+template <bool HALF, int R>
+__device__ __forceinline__ void cmv_adjoint4(const void* __restrict__ Dc, int a, int nc, const float2 (*xs)[CMV_KMAX],
+                                             float2* __restrict__ tau, size_t rs, int live) {
     const int nv = nc / 2;
     for (int o = threadIdx.x; o < 4 * nc; o += CMV_TPB) {
         const int mu = o / nc, i = o % nc;
         const size_t base = (((size_t)a * 9 + 2 + 2 * mu) * nc + i) * nc;
-        float re = 0.f, im = 0.f;
+        float re[R], im[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) re[j] = im[j] = 0.f;
         for (int c = 0; c < nc; ++c) {
             const float2 m = cm_load<HALF>(Dc, base + c);
-            const float2 x = xa[c];
             const float sg = (i < nv) == (c < nv) ? 1.f : -1.f;
-            // conj(m) x
-            re = fmaf(sg * m.x, x.x, re); re = fmaf(sg * m.y, x.y, re);
-            im = fmaf(sg * m.x, x.y, im); im = fmaf(-sg * m.y, x.x, im);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const float2 x = xs[j][c];
+                // conj(m) x
+                re[j] = fmaf(sg * m.x, x.x, re[j]); re[j] = fmaf(sg * m.y, x.y, re[j]);
+                im[j] = fmaf(sg * m.x, x.y, im[j]); im[j] = fmaf(-sg * m.y, x.x, im[j]);
+            }
         }
-        tau[((size_t)a * 4 + mu) * nc + i] = make_float2(re, im);
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (live >> j & 1) tau[j * rs + ((size_t)a * 4 + mu) * nc + i] = make_float2(re[j], im[j]);
     }
 }
 
@@ -506,45 +530,71 @@ __device__ __forceinline__ float group_sum(float v) {
 // g5(col) g5(row) conj(M[k][row]) xa[row] and a group sum gives
 // tau[a][mu][col] for the -mu slots (it is formed, and dropped, for the
 // self slot too, so that every lane takes part in every exchange).  The
-// loads of a lane are issued in batches (5 FP32 or 10 FP16 entries) before
-// their arithmetic, and the sums are stored after the loop, so no store
-// sits between loads.
+// loads of a lane are issued in batches before their arithmetic, the first
+// batch (for one right-hand side and nc = 16 or 32 all of them) before the
+// entries of x are gathered, so that the two waits overlap; the sums are stored after the
+// loop, so no store sits between loads.
 // The forward chunks are reduced as in cmv_rows5.
-template <bool HALF, int NC>
-__device__ __forceinline__ float2 cmv5_fused(const void* __restrict__ Dc, int a, const float2* xs, float2* red,
-                                             float2* __restrict__ tau) {
-    constexpr int KCH = CMV_TPB / NC, NJ = 5 * NC / KCH, NV = NC / 2;
-    // loads issued together before their arithmetic (NJ is 5, 20 or 80)
-    constexpr int CH = NJ < (HALF ? 10 : 5) ? NJ : (HALF ? 10 : 5);
+template <bool HALF, int NC, int R>
+struct FusedBatch {
+    static constexpr int KCH = CMV_TPB / NC, NJ = 5 * NC / KCH;  // NJ is 5, 20 or 80
+    static constexpr int MOST = R == 1 ? 20 : 10, CH = NJ < MOST ? NJ : MOST;  // entries of a batch
     static_assert(NJ % CH == 0 && NJ <= 2 * NC, "batches cover the loop; a lane keeps at most two sums");
-    const int t = threadIdx.x, row = t % NC, kc = t / NC;
-    const size_t base = (size_t)a * 9 * NC * NC + row;
-    const float2 xa = xs[row];
-    float re = 0.f, im = 0.f;
-    // the adjoint sums this lane stores: j = row and j = row + NC
-    float2 keep0 = make_float2(0.f, 0.f), keep1 = make_float2(0.f, 0.f);
-#pragma unroll 1
-    for (int j0 = 0; j0 < NJ; j0 += CH) {
-        float2 m[CH];
+    float2 m[CH];
+    __device__ __forceinline__ void load(const void* __restrict__ Dc, int a, int j0) {
+        const int row = threadIdx.x % NC, kc = threadIdx.x / NC;
+        const size_t base = (size_t)a * 9 * NC * NC + row;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int k = kc + (j0 + c) * KCH;
             m[c] = cm_load<HALF>(Dc, base + (size_t)(slot_dir(k / NC) * NC + k % NC) * NC);
         }
+    }
+};
+
+template <bool HALF, int NC, int R>
+__device__ __forceinline__ void cmv5_fused(const void* __restrict__ Dc, int a, FusedBatch<HALF, NC, R>& fb,
+                                           const float2 (*xs)[CMV_KMAX], float2* red, float2* __restrict__ tau,
+                                           size_t rs, int live, float2* y) {
+    using FB = FusedBatch<HALF, NC, R>;
+    constexpr int KCH = FB::KCH, NJ = FB::NJ, CH = FB::CH, NV = NC / 2;
+    const int t = threadIdx.x, row = t % NC, kc = t / NC;
+    float2 xa[R];
+    float re[R], im[R];
+    // the adjoint sums this lane stores: j = row and j = row + NC
+    float2 keep0[R], keep1[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        xa[q] = xs[q][row];
+        re[q] = im[q] = 0.f;
+        keep0[q] = keep1[q] = make_float2(0.f, 0.f);
+    }
+#pragma unroll 1
+    for (int j0 = 0; j0 < NJ; j0 += CH) {
+        if (j0 > 0) fb.load(Dc, a, j0);
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int j = j0 + c, k = kc + j * KCH, col = k % NC;
-            const float2 x = xs[k];
-            re = fmaf(m[c].x, x.x, re);
-            re = fmaf(-m[c].y, x.y, re);
-            im = fmaf(m[c].x, x.y, im);
-            im = fmaf(m[c].y, x.x, im);
+            const float2 m = fb.m[c];
             const float sg = (col < NV) == (row < NV) ? 1.f : -1.f;
-            float ar = sg * fmaf(m[c].x, xa.x, m[c].y * xa.y), ai = sg * fmaf(m[c].x, xa.y, -m[c].y * xa.x);
-            ar = group_sum<NC>(ar);
-            ai = group_sum<NC>(ai);
-            if (j == row) keep0 = make_float2(ar, ai);
-            if (j == row + NC) keep1 = make_float2(ar, ai);
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const float2 x = xs[q][k];
+                re[q] = fmaf(m.x, x.x, re[q]);
+                re[q] = fmaf(-m.y, x.y, re[q]);
+                im[q] = fmaf(m.x, x.y, im[q]);
+                im[q] = fmaf(m.y, x.x, im[q]);
+                float ar = sg * fmaf(m.x, xa[q].x, m.y * xa[q].y), ai = sg * fmaf(m.x, xa[q].y, -m.y * xa[q].x);
+                ar = group_sum<NC>(ar);
+                ai = group_sum<NC>(ai);
+                if (j == row) keep0[q] = make_float2(ar, ai);
+                if (j == row + NC) keep1[q] = make_float2(ar, ai);
+            }
+            // the selections are made here: left to the end of the batch they
+            // would keep all of its sums in registers
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                asm volatile("" : "+v"(keep0[q].x), "+v"(keep0[q].y), "+v"(keep1[q].x), "+v"(keep1[q].y));
         }
     }
 #pragma unroll
@@ -552,31 +602,43 @@ __device__ __forceinline__ float2 cmv5_fused(const void* __restrict__ Dc, int a,
         const int j = i * NC + row;
         if (j < NJ) {
             const int k = kc + j * KCH, sl = k / NC;
-            if (sl > 0) tau[((size_t)a * 4 + sl - 1) * NC + k % NC] = i ? keep1 : keep0;
+            if (sl > 0) {
+#pragma unroll
+                for (int q = 0; q < R; ++q)
+                    if (live >> q & 1) tau[q * rs + ((size_t)a * 4 + sl - 1) * NC + k % NC] = i ? keep1[q] : keep0[q];
+            }
         }
     }
-    red[t] = make_float2(re, im);
-    __syncthreads();
-    float2 y = make_float2(0.f, 0.f);
-    if (t < NC)
-        for (int c = 0; c < KCH; ++c) {
-            const float2 v = red[c * NC + t];
-            y.x += v.x;
-            y.y += v.y;
-        }
-    return y;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        if (q > 0) __syncthreads();  // the previous right-hand side's readers of red are done
+        red[t] = make_float2(re[q], im[q]);
+        __syncthreads();
+        y[q] = make_float2(0.f, 0.f);
+        if (t < NC)
+            for (int c = 0; c < KCH; ++c) {
+                const float2 v = red[c * NC + t];
+                y[q].x += v.x;
+                y[q].y += v.y;
+            }
+    }
 }
 
-// Pass 1 for any nc: NC = 0 takes the two-step form
-template <bool HALF, int NC>
-__device__ __forceinline__ float2 cmv5(const void* __restrict__ Dc, int a, int nc, const float2* xs, float2* red,
-                                       float2* __restrict__ tau) {
+// Pass 1 for any nc: NC = 0 takes the two-step form.  gather() fills xs and
+// returns after every lane can read it.
+template <bool HALF, int NC, int R, typename G>
+__device__ __forceinline__ void cmv5(const void* __restrict__ Dc, int a, int nc, const float2 (*xs)[CMV_KMAX],
+                                     float2* red, float2* __restrict__ tau, size_t rs, int live, float2* y,
+                                     G&& gather) {
     if constexpr (NC > 0) {
-        return cmv5_fused<HALF, NC>(Dc, a, xs, red, tau);
+        FusedBatch<HALF, NC, R> fb;
+        fb.load(Dc, a, 0);
+        gather();
+        cmv5_fused<HALF, NC, R>(Dc, a, fb, xs, red, tau, rs, live, y);
     } else {
-        const float2 y = cmv_rows5<HALF>(Dc, a, nc, xs, red);
-        cmv_adjoint4<HALF>(Dc, a, nc, xs, tau);
-        return y;
+        gather();
+        cmv_rows5<HALF, R>(Dc, a, nc, xs, red, y);
+        cmv_adjoint4<HALF, R>(Dc, a, nc, xs, tau, rs, live);
     }
 }
 
@@ -611,14 +673,16 @@ template <bool HALF, int NC>
 __global__ __launch_bounds__(CMV_TPB) void k_mg_coarse_apply(Geom g, const void* __restrict__ Dc, int nc,
                                                              const float2* __restrict__ x, float2* __restrict__ y,
                                                              float2* __restrict__ tau) {
-    __shared__ float2 xs[CMV_KMAX];
+    __shared__ float2 xs[1][CMV_KMAX];
     __shared__ float2 red[CMV_TPB];
     const int a = blockIdx.x, K5 = 5 * nc;
     const BlockPos p = block_pos(g, a);
-    for (int k = threadIdx.x; k < K5; k += CMV_TPB) xs[k] = x[gather_index(g, p, nc, k)];
-    __syncthreads();
-    const float2 v = cmv5<HALF, NC>(Dc, a, nc, xs, red, tau);
-    if ((int)threadIdx.x < nc) y[(size_t)a * nc + threadIdx.x] = v;
+    float2 v[1];
+    cmv5<HALF, NC, 1>(Dc, a, nc, xs, red, tau, 0, 1, v, [&]() {
+        for (int k = threadIdx.x; k < K5; k += CMV_TPB) xs[0][k] = x[gather_index(g, p, nc, k)];
+        __syncthreads();
+    });
+    if ((int)threadIdx.x < nc) y[(size_t)a * nc + threadIdx.x] = v[0];
 }
 
 // y = D_c x, pass 2
@@ -640,7 +704,10 @@ __device__ __forceinline__ double2 cmul_d(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// Coarse BiCGStab.  The start (x = 0, r = rh = r_c) is followed by the stop
+// Coarse BiCGStab, for one right-hand side or for several at once (each with
+// its own vectors cv.rs apart, scalars, partial sums and stops; the second
+// grid dimension, or the first of the one-workgroup kernels, runs over them).
+// The start (x = 0, r = rh = r_c) is followed by the stop
 // test F1 of iteration 0; iteration it (parity q = it & 1) is then eight
 // launches, the last of which is the stop test of iteration it + 1:
 //   M1  p = r + beta (p_prev - omega v_prev) formed while gathering, pass 1
@@ -693,6 +760,8 @@ __device__ __forceinline__ void sum3_partials(const double2* partials, int nwg, 
 __global__ __launch_bounds__(1024) void k_cb_f1(const double2* partials, int nwg, CbScalars* sc, int it,
                                                 double tol2) {
     const int q = it & 1;
+    partials += (size_t)blockIdx.x * CB_PARTIALS;
+    sc += blockIdx.x;
     double tot[3];
     sum3_partials(partials, nwg, tot);
     if (threadIdx.x != 0) return;
@@ -729,6 +798,7 @@ __device__ __forceinline__ void chunk_partials(double2 a, double b, double2* par
     }
     __syncthreads();
     if (threadIdx.x == 0) {
+        partials += (size_t)blockIdx.y * CB_PARTIALS;
         partials[(size_t)blockIdx.x * 2] = make_double2((red[0][0] + red[0][1]) + (red[0][2] + red[0][3]),
                                                         (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
         partials[(size_t)blockIdx.x * 2 + 1] =
@@ -736,37 +806,51 @@ __device__ __forceinline__ void chunk_partials(double2 a, double b, double2* par
     }
 }
 
-template <bool HALF, int NC>
+template <bool HALF, int NC, int R>
 __global__ __launch_bounds__(CMV_TPB) void k_cb_m1(Geom g, const void* __restrict__ Dc, int nc, CbVecs cv,
-                                                   const CbScalars* sc, int q) {
-    if (sc->stopped[q]) return;
-    __shared__ float2 xs[CMV_KMAX];
+                                                   const CbScalars* sc, int q, int nr) {
+    const int r0 = blockIdx.y * R;
+    int live = 0;  // bit j: right-hand side r0 + j is still being solved
+    for (int j = 0; j < R; ++j) live |= (r0 + j < nr && !sc[r0 + j].stopped[q]) << j;
+    if (!live) return;
+    __shared__ float2 xs[R][CMV_KMAX];
     __shared__ float2 red[CMV_TPB];
     const int a = blockIdx.x, K5 = 5 * nc;
     const BlockPos p = block_pos(g, a);
-    const float br = (float)sc->beta[q].x, bi = (float)sc->beta[q].y;
-    const float wr = (float)sc->omega.x, wi = (float)sc->omega.y;
-    const float2 *pp = cv.p[q ^ 1], *vp = cv.v[q ^ 1];
-    float2* pn = cv.p[q];
-    for (int k = threadIdx.x; k < K5; k += CMV_TPB) {
-        const size_t i = gather_index(g, p, nc, k);
-        const float2 r = cv.r[i], po = pp[i], vo = vp[i];
-        const float tr = po.x - (wr * vo.x - wi * vo.y), ti = po.y - (wr * vo.y + wi * vo.x);
-        const float2 pv = make_float2(r.x + (br * tr - bi * ti), r.y + (br * ti + bi * tr));
-        xs[k] = pv;
-        if (k < nc) pn[i] = pv;
-    }
-    __syncthreads();
-    const float2 v = cmv5<HALF, NC>(Dc, a, nc, xs, red, cv.tau);
-    if ((int)threadIdx.x < nc) cv.v[q][(size_t)a * nc + threadIdx.x] = v;
+    float2 v[R];
+    cmv5<HALF, NC, R>(Dc, a, nc, xs, red, cv.tau + r0 * cv.rs, cv.rs, live, v, [&]() {
+        for (int j = 0; j < R; ++j) {
+            if (!(live >> j & 1)) continue;  // xs[j] goes into no stored value then
+            const CbScalars& S = sc[r0 + j];
+            const float br = (float)S.beta[q].x, bi = (float)S.beta[q].y;
+            const float wr = (float)S.omega.x, wi = (float)S.omega.y;
+            const size_t o = (r0 + j) * cv.rs;
+            const float2 *rp = cv.r + o, *pp = cv.pp(q ^ 1) + o, *vp = cv.vv(q ^ 1) + o;
+            float2* pn = cv.pp(q) + o;
+            for (int k = threadIdx.x; k < K5; k += CMV_TPB) {
+                const size_t i = gather_index(g, p, nc, k);
+                const float2 r = rp[i], po = pp[i], vo = vp[i];
+                const float tr = po.x - (wr * vo.x - wi * vo.y), ti = po.y - (wr * vo.y + wi * vo.x);
+                const float2 pv = make_float2(r.x + (br * tr - bi * ti), r.y + (br * ti + bi * tr));
+                xs[j][k] = pv;
+                if (k < nc) pn[i] = pv;
+            }
+        }
+        __syncthreads();
+    });
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        if ((live >> j & 1) && (int)threadIdx.x < nc) cv.vv(q)[(r0 + j) * cv.rs + (size_t)a * nc + threadIdx.x] = v[j];
 }
 
 // v += the +mu terms, partials B of <rh, v>
 __global__ __launch_bounds__(256) void k_cb_c1(Geom g, int nc, CbVecs cv, const CbScalars* sc, int q,
                                                double2* partials) {
+    sc += blockIdx.y;
     if (sc->stopped[q]) return;
+    cv = cv.of(blockIdx.y);
     const size_t n = (size_t)g.nblk * nc;
-    float2* vq = cv.v[q];
+    float2* vq = cv.vv(q);
     double2 d = make_double2(0.0, 0.0);
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
         const float2 t = tau_sum(g, nc, cv.tau, i), v0 = vq[i];
@@ -780,6 +864,8 @@ __global__ __launch_bounds__(256) void k_cb_c1(Geom g, int nc, CbVecs cv, const 
 }
 
 __global__ __launch_bounds__(1024) void k_cb_f2(const double2* partials, int nwg, CbScalars* sc, int q) {
+    partials += (size_t)blockIdx.x * CB_PARTIALS;
+    sc += blockIdx.x;
     if (sc->stopped[q]) return;
     double tot[3];
     sum3_partials(partials, nwg, tot);
@@ -790,32 +876,46 @@ __global__ __launch_bounds__(1024) void k_cb_f2(const double2* partials, int nwg
     if (!brk) sc->alpha = cdiv2(sc->rho[q], rv);
 }
 
-template <bool HALF, int NC>
+template <bool HALF, int NC, int R>
 __global__ __launch_bounds__(CMV_TPB) void k_cb_m2(Geom g, const void* __restrict__ Dc, int nc, CbVecs cv,
-                                                   const CbScalars* sc, int q) {
-    if (sc->stopped[q] || sc->brk[q]) return;
-    __shared__ float2 xs[CMV_KMAX];
+                                                   const CbScalars* sc, int q, int nr) {
+    const int r0 = blockIdx.y * R;
+    int live = 0;
+    for (int j = 0; j < R; ++j) live |= (r0 + j < nr && !sc[r0 + j].stopped[q] && !sc[r0 + j].brk[q]) << j;
+    if (!live) return;
+    __shared__ float2 xs[R][CMV_KMAX];
     __shared__ float2 red[CMV_TPB];
     const int a = blockIdx.x, K5 = 5 * nc;
     const BlockPos p = block_pos(g, a);
-    const float ar = (float)sc->alpha.x, ai = (float)sc->alpha.y;
-    const float2* vq = cv.v[q];
-    for (int k = threadIdx.x; k < K5; k += CMV_TPB) {
-        const size_t i = gather_index(g, p, nc, k);
-        const float2 r = cv.r[i], v = vq[i];
-        const float2 sv = make_float2(r.x - (ar * v.x - ai * v.y), r.y - (ar * v.y + ai * v.x));
-        xs[k] = sv;
-        if (k < nc) cv.s[i] = sv;
-    }
-    __syncthreads();
-    const float2 tv = cmv5<HALF, NC>(Dc, a, nc, xs, red, cv.tau);
-    if ((int)threadIdx.x < nc) cv.t[(size_t)a * nc + threadIdx.x] = tv;
+    float2 t[R];
+    cmv5<HALF, NC, R>(Dc, a, nc, xs, red, cv.tau + r0 * cv.rs, cv.rs, live, t, [&]() {
+        for (int j = 0; j < R; ++j) {
+            if (!(live >> j & 1)) continue;
+            const float ar = (float)sc[r0 + j].alpha.x, ai = (float)sc[r0 + j].alpha.y;
+            const size_t o = (r0 + j) * cv.rs;
+            const float2 *rp = cv.r + o, *vq = cv.vv(q) + o;
+            float2* sp = cv.s + o;
+            for (int k = threadIdx.x; k < K5; k += CMV_TPB) {
+                const size_t i = gather_index(g, p, nc, k);
+                const float2 r = rp[i], v = vq[i];
+                const float2 sv = make_float2(r.x - (ar * v.x - ai * v.y), r.y - (ar * v.y + ai * v.x));
+                xs[j][k] = sv;
+                if (k < nc) sp[i] = sv;
+            }
+        }
+        __syncthreads();
+    });
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        if ((live >> j & 1) && (int)threadIdx.x < nc) cv.t[(r0 + j) * cv.rs + (size_t)a * nc + threadIdx.x] = t[j];
 }
 
 // t += the +mu terms, partials C of <t, s>, |t|^2
 __global__ __launch_bounds__(256) void k_cb_c2(Geom g, int nc, CbVecs cv, const CbScalars* sc, int q,
                                                double2* partials) {
+    sc += blockIdx.y;
     if (sc->stopped[q] || sc->brk[q]) return;
+    cv = cv.of(blockIdx.y);
     const size_t n = (size_t)g.nblk * nc;
     double2 ts = make_double2(0.0, 0.0);
     double tt = 0.0;
@@ -832,6 +932,8 @@ __global__ __launch_bounds__(256) void k_cb_c2(Geom g, int nc, CbVecs cv, const 
 }
 
 __global__ __launch_bounds__(1024) void k_cb_f3(const double2* partials, int nwg, CbScalars* sc, int q) {
+    partials += (size_t)blockIdx.x * CB_PARTIALS;
+    sc += blockIdx.x;
     if (sc->stopped[q] || sc->brk[q]) return;
     double tot[3];
     sum3_partials(partials, nwg, tot);
@@ -842,6 +944,8 @@ __global__ __launch_bounds__(1024) void k_cb_f3(const double2* partials, int nwg
 
 // x = 0, r = rh = rc, p_prev = v_prev = 0 (slot 1), partials A
 __global__ __launch_bounds__(256) void k_cb_init(int n, const float2* rc, CbVecs cv, double2* partials) {
+    cv = cv.of(blockIdx.y);
+    rc += (size_t)blockIdx.y * n;
     double2 a = make_double2(0.0, 0.0);
     double b = 0.0;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
@@ -857,9 +961,11 @@ __global__ __launch_bounds__(256) void k_cb_init(int n, const float2* rc, CbVecs
 
 __global__ __launch_bounds__(256) void k_cb_update(int n, const CbScalars* sc, int q, CbVecs cv,
                                                    double2* partials) {
+    sc += blockIdx.y;
     if (sc->stopped[q] || sc->brk[q]) return;
+    cv = cv.of(blockIdx.y);
     const float ar = (float)sc->alpha.x, ai = (float)sc->alpha.y, wr = (float)sc->omega.x, wi = (float)sc->omega.y;
-    const float2* pq = cv.p[q];
+    const float2* pq = cv.pp(q);
     double2 a = make_double2(0.0, 0.0);
     double b = 0.0;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
@@ -961,11 +1067,11 @@ hipError_t mg_restrict_many(const Geom& g, Transfer T, int nv, const void* r, in
     return hipGetLastError();
 }
 
-hipError_t mg_prolong_many(const Geom& g, Transfer T, int nv, const float2* ec, int nr, void* z, hipStream_t s) {
+hipError_t mg_prolong_many(const Geom& g, Transfer T, int nv, const float2* ec, size_t ecs, int nr, void* z,
+                           hipStream_t s) {
     ProfScope ps("mg", s);
     constexpr int R = 4;
     const size_t fs = spinor_bytes_per_site(T.prec) * g.V, zs = spinor_bytes_per_site(P_F32) * g.V;
-    const size_t ecs = (size_t)g.nblk * 2 * nv;
     const dim3 grid(g.nblk, (nr + R - 1) / R);
     if (T.prec == P_F16)
         hipLaunchKernelGGL((k_mg_prolong_many<P_F16, R>), grid, dim3(TPB), 0, s, g, (const char*)T.P, fs, nv, ec,
@@ -1008,37 +1114,54 @@ hipError_t mg_coarse_apply(const Geom& g, CoarseMat M, int nc, const float2* x, 
         CB_CHECK();                              \
     } while (0)
 
-hipError_t mg_coarse_begin(const Geom& g, int nc, const float2* rc, const CbVecs& cv, CbScalars* sc,
+// Right-hand sides that share one pass over D_c in a batch: four, so that the
+// sums and kept adjoints of a lane (7 floats each) stay in registers beside
+// the loads in flight.  At 16^3 x 32 with 16 null vectors a product of all 16
+// takes 57 us, one alone 20; the coarse solves of four adaptive passes 2 ms
+// side by side, 14 one after another.
+constexpr int CB_BATCH = 4;
+
+hipError_t mg_coarse_begin(const Geom& g, int nc, int nr, const float2* rc, const CbVecs& cv, CbScalars* sc,
                            const CbPartials& pa, double tol, hipStream_t s) {
     ProfScope ps("mg", s);
     const int n = g.nblk * nc, grid = cb_grid(n);
-    CB_LAUNCH(k_cb_init, dim3(grid), dim3(256), 0, s, n, rc, cv, pa.A);
-    CB_LAUNCH(k_cb_f1, dim3(1), dim3(1024), 0, s, pa.A, grid, sc, 0, tol * tol);
+    CB_LAUNCH(k_cb_init, dim3(grid, nr), dim3(256), 0, s, n, rc, cv, pa.A);
+    CB_LAUNCH(k_cb_f1, dim3(nr), dim3(1024), 0, s, pa.A, grid, sc, 0, tol * tol);
     return hipSuccess;
 }
 
-hipError_t mg_coarse_iters(const Geom& g, CoarseMat M, int nc, const CbVecs& cv, CbScalars* sc,
+hipError_t mg_coarse_iters(const Geom& g, CoarseMat M, int nc, int nr, const CbVecs& cv, CbScalars* sc,
                            const CbPartials& pa, int it0, int it1, hipStream_t s) {
     ProfScope ps("mg", s);
     const int n = g.nblk * nc, grid = cb_grid(n);
+    // pass 1 of a product: one right-hand side per workgroup, or CB_BATCH
+    auto product = [&](auto m1, int q) {
+        with_nc(nc, M.half, [&](auto half, auto ncc) {
+            constexpr bool H = decltype(half)::value;
+            constexpr int NC = decltype(ncc)::value;
+            if (nr == 1) {
+                const dim3 wgs(g.nblk);
+                if constexpr (decltype(m1)::value) hipLaunchKernelGGL((k_cb_m1<H, NC, 1>), wgs, dim3(CMV_TPB), 0, s, g, M.m, nc, cv, sc, q, nr);
+                else hipLaunchKernelGGL((k_cb_m2<H, NC, 1>), wgs, dim3(CMV_TPB), 0, s, g, M.m, nc, cv, sc, q, nr);
+            } else {
+                const dim3 wgs(g.nblk, (nr + CB_BATCH - 1) / CB_BATCH);
+                if constexpr (decltype(m1)::value) hipLaunchKernelGGL((k_cb_m1<H, NC, CB_BATCH>), wgs, dim3(CMV_TPB), 0, s, g, M.m, nc, cv, sc, q, nr);
+                else hipLaunchKernelGGL((k_cb_m2<H, NC, CB_BATCH>), wgs, dim3(CMV_TPB), 0, s, g, M.m, nc, cv, sc, q, nr);
+            }
+        });
+    };
     for (int it = it0; it < it1; ++it) {
         const int q = it & 1;
-        with_nc(nc, M.half, [&](auto half, auto ncc) {
-            hipLaunchKernelGGL((k_cb_m1<decltype(half)::value, decltype(ncc)::value>), dim3(g.nblk), dim3(CMV_TPB),
-                               0, s, g, M.m, nc, cv, sc, q);
-        });
+        product(std::true_type{}, q);
         CB_CHECK();
-        CB_LAUNCH(k_cb_c1, dim3(grid), dim3(256), 0, s, g, nc, cv, sc, q, pa.B);
-        CB_LAUNCH(k_cb_f2, dim3(1), dim3(1024), 0, s, pa.B, grid, sc, q);
-        with_nc(nc, M.half, [&](auto half, auto ncc) {
-            hipLaunchKernelGGL((k_cb_m2<decltype(half)::value, decltype(ncc)::value>), dim3(g.nblk), dim3(CMV_TPB),
-                               0, s, g, M.m, nc, cv, sc, q);
-        });
+        CB_LAUNCH(k_cb_c1, dim3(grid, nr), dim3(256), 0, s, g, nc, cv, sc, q, pa.B);
+        CB_LAUNCH(k_cb_f2, dim3(nr), dim3(1024), 0, s, pa.B, grid, sc, q);
+        product(std::false_type{}, q);
         CB_CHECK();
-        CB_LAUNCH(k_cb_c2, dim3(grid), dim3(256), 0, s, g, nc, cv, sc, q, pa.C);
-        CB_LAUNCH(k_cb_f3, dim3(1), dim3(1024), 0, s, pa.C, grid, sc, q);
-        CB_LAUNCH(k_cb_update, dim3(grid), dim3(256), 0, s, n, sc, q, cv, pa.A);
-        CB_LAUNCH(k_cb_f1, dim3(1), dim3(1024), 0, s, pa.A, grid, sc, it + 1, 0.0);
+        CB_LAUNCH(k_cb_c2, dim3(grid, nr), dim3(256), 0, s, g, nc, cv, sc, q, pa.C);
+        CB_LAUNCH(k_cb_f3, dim3(nr), dim3(1024), 0, s, pa.C, grid, sc, q);
+        CB_LAUNCH(k_cb_update, dim3(grid, nr), dim3(256), 0, s, n, sc, q, cv, pa.A);
+        CB_LAUNCH(k_cb_f1, dim3(nr), dim3(1024), 0, s, pa.A, grid, sc, it + 1, 0.0);
     }
     return hipSuccess;
 }
@@ -1048,9 +1171,9 @@ hipError_t mg_coarse_iters(const Geom& g, CoarseMat M, int nc, const CbVecs& cv,
 
 hipError_t mg_coarse_bicgstab(const Geom& g, CoarseMat M, int nc, const float2* rc, const CbVecs& cv,
                               CbScalars* sc, const CbPartials& pa, int max_iter, double tol, hipStream_t s) {
-    hipError_t e = mg_coarse_begin(g, nc, rc, cv, sc, pa, tol, s);
+    hipError_t e = mg_coarse_begin(g, nc, 1, rc, cv, sc, pa, tol, s);
     if (e != hipSuccess) return e;
-    return mg_coarse_iters(g, M, nc, cv, sc, pa, 0, max_iter, s);
+    return mg_coarse_iters(g, M, nc, 1, cv, sc, pa, 0, max_iter, s);
 }
 
 }  // namespace cs

@@ -23,13 +23,39 @@ struct CbScalars {
     int stopped[2], brk[2];
 };
 
+constexpr int CB_VECS = 13;  // coarse vectors of one right-hand side: the nine below and tau (four)
 struct CbVecs {
     float2 *x, *r, *rh, *p[2], *v[2], *s, *t;
-    float2* tau;  // the +mu terms of a product, [aggregate][mu][nc]
+    float2* tau;   // the +mu terms of a product, [aggregate][mu][nc]
+    size_t rs = 0; // entries from one right-hand side's vectors to the next one's
+    // p and v of parity q by selection: an index known only at run time would
+    // put the struct into memory
+    __device__ float2* pp(int q) const { return q ? p[1] : p[0]; }
+    __device__ float2* vv(int q) const { return q ? v[1] : v[0]; }
+    // the vectors of right-hand side 0 in a buffer of n entries each
+    void place(float2* base, size_t n) {
+        x = base;
+        r = base + n;
+        rh = base + 2 * n;
+        p[0] = base + 3 * n;
+        p[1] = base + 4 * n;
+        v[0] = base + 5 * n;
+        v[1] = base + 6 * n;
+        s = base + 7 * n;
+        t = base + 8 * n;
+        tau = base + 9 * n;
+        rs = CB_VECS * n;
+    }
+    __host__ __device__ CbVecs of(int i) const {
+        const size_t o = i * rs;
+        return {x + o, r + o, rh + o, {p[0] + o, p[1] + o}, {v[0] + o, v[1] + o}, s + o, t + o, tau + o, rs};
+    }
 };
 
 // Workgroup partial sums of the elementwise kernels (at most MG_ELEM_WG
-// workgroups each): A of <rh, r>, |r|^2, B of <rh, v>, C of <t, s>, |t|^2.
+// workgroups each): A of <rh, r>, |r|^2, B of <rh, v>, C of <t, s>, |t|^2;
+// the arrays of one right-hand side after another.
+constexpr size_t CB_PARTIALS = 2 * (size_t)MG_ELEM_WG;  // entries of one array
 struct CbPartials {
     double2 *A, *B, *C;
 };
@@ -70,7 +96,7 @@ struct MgData {
     CbScalars* sc = nullptr;
     CbPartials pa{};
     LaunchCfg sap_cfg{};
-    int* host_flag = nullptr;  // pinned copy of a stop flag
+    CbScalars* host_sc = nullptr;  // pinned copies of the scalars (stop flags) of up to nv solves
     unsigned long long id = 0; // distinct for every allocation (keys of captured graphs)
     // captured graphs of the coarse phase, one set per input field `r`:
     // restriction of r, start and the first chunk; then chunk j covers
@@ -104,7 +130,8 @@ hipError_t mg_prolong(const Geom& g, Transfer T, int nv, const float2* ec, void*
 // the one-field launches
 hipError_t mg_restrict_many(const Geom& g, Transfer T, int nv, const void* r, int nr, float2* rc,
                             hipStream_t s);
-hipError_t mg_prolong_many(const Geom& g, Transfer T, int nv, const float2* ec, int nr, void* z, hipStream_t s);
+hipError_t mg_prolong_many(const Geom& g, Transfer T, int nv, const float2* ec, size_t ecs, int nr, void* z,
+                           hipStream_t s);
 // Dc16 = FP16 copy of the n complex entries of Dc
 hipError_t mg_coarse_half(const float2* Dc, void* Dc16, size_t n, hipStream_t s);
 // y = D_c x
@@ -114,11 +141,13 @@ hipError_t mg_coarse_apply(const Geom& g, CoarseMat M, int nc, const float2* x, 
 // |r| <= tol |rc| or on a breakdown (all decided on the device)
 hipError_t mg_coarse_bicgstab(const Geom& g, CoarseMat M, int nc, const float2* rc, const CbVecs& cv,
                               CbScalars* sc, const CbPartials& pa, int max_iter, double tol, hipStream_t s);
-// The same solve in pieces: the start with the stop test of iteration 0, then
-// iterations [it0, it1), each ending with the stop test of the next one.
-hipError_t mg_coarse_begin(const Geom& g, int nc, const float2* rc, const CbVecs& cv, CbScalars* sc,
+// The same solve in pieces, for nr right-hand sides at once (rc: nr consecutive
+// coarse vectors; cv, sc and pa hold nr sets): the start with the stop test of
+// iteration 0, then iterations [it0, it1), each ending with the stop test of
+// the next one.
+hipError_t mg_coarse_begin(const Geom& g, int nc, int nr, const float2* rc, const CbVecs& cv, CbScalars* sc,
                            const CbPartials& pa, double tol, hipStream_t s);
-hipError_t mg_coarse_iters(const Geom& g, CoarseMat M, int nc, const CbVecs& cv, CbScalars* sc,
+hipError_t mg_coarse_iters(const Geom& g, CoarseMat M, int nc, int nr, const CbVecs& cv, CbScalars* sc,
                            const CbPartials& pa, int it0, int it1, hipStream_t s);
 
 // mg.cpp
