@@ -173,13 +173,13 @@ typedef struct {
     int lanes_per_site;
 } cs_launch_config;
 
-/* Time the SAP half-sweep and the operator for rhs_tile in {1, 4, 8, 12}
- * (up to nrhs), for grid and persistent launches and (SAP below FP64) for
- * one and two lanes per site, on nrhs right-hand
- * sides of precision prec, and return the fastest shapes (either pointer may
- * be NULL).  The result is cached with the clover handle and used by
- * cs_gcr_solve when params.rhs_tile is 0.  Allocates and frees scratch
- * fields; synchronises the stream. */
+/* Time the SAP half-sweep and the operator for the rhs_tile values that fill
+ * the GPU's rounds of workgroups best (up to nrhs), for grid and persistent
+ * launches and (SAP below FP64, small batches) for one and two lanes per
+ * site, on nrhs right-hand sides of precision prec, and return the fastest
+ * shapes (either pointer may be NULL).  The result is cached with the clover
+ * handle and used by cs_gcr_solve when params.rhs_tile is 0.  Allocates and
+ * frees scratch fields; synchronises the stream. */
 int cs_autotune(cs_gauge g, cs_clover c, cs_prec prec, int nrhs, cs_launch_config* sap,
                 cs_launch_config* dslash, void* stream);
 
@@ -201,8 +201,9 @@ int cs_sap_smooth(cs_gauge g, cs_clover c, cs_prec prec, void* x, const void* b,
                   int n_cy, int n_mr, int x0_is_zero, int nrhs, void* stream);
 
 /* cs_sap_smooth and cs_apply_D with an explicit multi-right-hand-side launch
- * shape (cfg NULL: one right-hand side per workgroup).  Results are bitwise
- * identical to the untiled calls. */
+ * shape (cfg NULL: the library chooses from the lattice and nrhs, as
+ * cs_sap_smooth and cs_apply_D do).  Results are bitwise identical to the
+ * calls without one; lanes_per_site, where given, must be theirs. */
 int cs_sap_smooth_cfg(cs_gauge g, cs_clover c, cs_prec prec, void* x, const void* b,
                       int n_cy, int n_mr, int x0_is_zero, int nrhs,
                       const cs_launch_config* cfg, void* stream);

@@ -2,6 +2,7 @@
 // argument validation, error reporting and launch profiling.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -354,7 +355,7 @@ static int apply(cs_gauge g, cs_clover c, cs_prec prec, void* out, const void* i
     if (nrhs < 1 || nrhs > 65535) return fail(CS_ERR_INVALID, "nrhs must be in 1..65535");
     const size_t bytes = cs::spinor_bytes_per_site(prec) * (size_t)g->g.V * nrhs;
     if (overlap(in, out, bytes)) return fail(CS_ERR_INVALID, "out and in overlap");
-    const cs::LaunchCfg lc = to_cfg(cfg);
+    const cs::LaunchCfg lc = cfg ? to_cfg(cfg) : cs::dslash_default_cfg(g->g, prec, nrhs);
     if (lc.rhs_tile > 1 || lc.persistent_wgs > 0)
         CS_HIP(cs::launch_dslash_tiled(make_op(g, c), prec, dagger, out, in, nrhs, lc, (hipStream_t)stream));
     else
@@ -388,7 +389,8 @@ static int sap_common(cs_gauge g, cs_clover c, cs_prec prec, void* x, const void
     const size_t bytes = cs::spinor_bytes_per_site(prec) * (size_t)g->g.V * nrhs;
     if (overlap(b, x, bytes)) return fail(CS_ERR_INVALID, "x and b overlap");
     const cs::OpData op = make_op(g, c);
-    const cs::LaunchCfg lc = to_cfg(cfg);
+    cs::LaunchCfg lc = cfg ? to_cfg(cfg) : cs::sap_default_cfg(g->g, prec, nrhs, solver);
+    if (lc.lanes_per_site == 0) lc.lanes_per_site = cs::sap_default_lanes(g->g, prec, nrhs, solver);
     hipStream_t s = (hipStream_t)stream;
     if (n_cy == 0 && x0_is_zero) {
         CS_HIP(hipMemsetAsync(x, 0, bytes, s));
@@ -448,47 +450,61 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     hipError_t err = cs::blas_fill_pattern(bc, prec, bb, s);
-    std::vector<cs::LaunchCfg> cands;
-    for (int t : {1, 4, 8, 12}) {
-        if (t > nrhs) continue;
-        for (int pw : {0, 2 * cus})
-            for (int lanes : {1, 2}) {
-                if (lanes == 2 && prec == CS_F64) continue;
-                cs::LaunchCfg lc;
-                lc.rhs_tile = t;
-                lc.persistent_wgs = pw;
-                lc.lanes_per_site = lanes;
-                cands.push_back(lc);
+    // Candidates: the tiles whose model time is within 12 % of the least (the
+    // model leaves out caches and clocks; 1 always), as a grid of all work
+    // items and as a persistent one, and for the smoother one and two lanes
+    // per site while both can be the faster (sap_default_lanes).
+    struct Cand {
+        int kind;  // 0: smoother, 1: operator
+        cs::LaunchCfg lc;
+    };
+    std::vector<Cand> cands;
+    const bool both = prec != CS_F64 && (long long)(g->g.nblk / 2) * nrhs <= 512;
+    for (int kind = 0; kind < 2; ++kind)
+        for (int lanes = 1; lanes <= (kind == 0 && both ? 2 : 1); ++lanes) {
+            auto units = [&](int t) {
+                return kind == 0 ? cs::sap_tile_units(g->g, nrhs, t, lanes) : cs::dslash_tile_units(g->g, prec, nrhs, t);
+            };
+            const int most = nrhs < 64 ? nrhs : 64;
+            double least = units(1);
+            for (int t = 2; t <= most; ++t) least = std::min(least, units(t));
+            for (int t = 1; t <= most; ++t) {
+                if (t > 1 && units(t) > 1.12 * least) continue;
+                for (int pw : {0, 2 * cus}) {
+                    Cand c{kind, {}};
+                    c.lc.rhs_tile = t;
+                    c.lc.persistent_wgs = pw;
+                    c.lc.lanes_per_site = kind == 0 ? lanes : 0;
+                    cands.push_back(c);
+                }
             }
-    }
+        }
     float best_s = 1e30f, best_dd = 1e30f;
     cs::LaunchCfg bs, bd;
-    for (const cs::LaunchCfg& lc : cands) {
-        if (err != hipSuccess) break;
-        for (int kind = 0; kind < 2 && err == hipSuccess; ++kind) {
-            auto run = [&]() -> hipError_t {
-                if (kind == 0) {
-                    for (int h = 0; h < 4; ++h) {
-                        hipError_t e2 = cs::launch_sap_halfsweep(op, prec, h & 1, 4, h == 0 ? 1 : (h == 1 ? 2 : 0),
-                                                                 xb, bb, nrhs, lc, s);
-                        if (e2 != hipSuccess) return e2;
-                    }
-                    return hipSuccess;
+    for (const Cand& c : cands) {
+        const cs::LaunchCfg& lc = c.lc;
+        auto run = [&]() -> hipError_t {
+            if (c.kind == 0) {
+                for (int h = 0; h < 4; ++h) {
+                    hipError_t e2 = cs::launch_sap_halfsweep(op, prec, h & 1, 4, h == 0 ? 1 : (h == 1 ? 2 : 0),
+                                                             xb, bb, nrhs, lc, s);
+                    if (e2 != hipSuccess) return e2;
                 }
-                if (lc.rhs_tile > 1 || lc.persistent_wgs > 0) return cs::launch_dslash_tiled(op, prec, false, xb, bb, nrhs, lc, s);
-                return cs::launch_dslash(op, prec, prec, prec, false, xb, bb, nullptr, nrhs, s);
-            };
-            err = run();  // warm-up
-            if (err != hipSuccess) break;
-            hipEventRecord(e0, s);
-            for (int rep = 0; rep < 3 && err == hipSuccess; ++rep) err = run();
-            hipEventRecord(e1, s);
-            if (err == hipSuccess) err = hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (err == hipSuccess) hipEventElapsedTime(&ms, e0, e1);
-            if (kind == 0 && ms < best_s) { best_s = ms; bs = lc; }
-            if (kind == 1 && ms < best_dd) { best_dd = ms; bd = lc; bd.lanes_per_site = 0; }
-        }
+                return hipSuccess;
+            }
+            if (lc.rhs_tile > 1 || lc.persistent_wgs > 0) return cs::launch_dslash_tiled(op, prec, false, xb, bb, nrhs, lc, s);
+            return cs::launch_dslash(op, prec, prec, prec, false, xb, bb, nullptr, nrhs, s);
+        };
+        if (err == hipSuccess) err = run();  // warm-up
+        if (err != hipSuccess) break;
+        hipEventRecord(e0, s);
+        for (int rep = 0; rep < 3 && err == hipSuccess; ++rep) err = run();
+        hipEventRecord(e1, s);
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (err == hipSuccess) hipEventElapsedTime(&ms, e0, e1);
+        if (c.kind == 0 && ms < best_s) { best_s = ms; bs = lc; }
+        if (c.kind == 1 && ms < best_dd) { best_dd = ms; bd = lc; }
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);

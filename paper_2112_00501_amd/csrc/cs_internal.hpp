@@ -436,10 +436,38 @@ struct LaunchCfg {
     int lanes_per_site = 0;
 };
 
+// Tile of right-hand sides for a launch over `blocks` blocks with `slots`
+// workgroups on the GPU at a time, from a model that the measured times follow
+// to about 5 %: a workgroup takes head + tile units (head: what it loads once
+// for its tile), and the launch as many rounds as the slots need for all
+// workgroups, so a tile that leaves a round nearly empty loses to one that
+// fills it (12 right-hand sides of 512 blocks in 512 slots: tiles of 4 and 8
+// take 137 and 154 us for the FP32 operator, 6 and 12 take 127 and 118).
+// *units: the model's time.
+inline int tile_for(long long blocks, int nrhs, int slots, double head, double* units) {
+    int best = 1;
+    double least = 0;
+    for (int t = 1; t <= nrhs && t <= 64; ++t) {
+        const long long wgs = blocks * ((nrhs + t - 1) / t);
+        const double u = (double)((wgs + slots - 1) / slots) * (head + t);
+        if (t == 1 || u < least) {
+            least = u;
+            best = t;
+        }
+    }
+    if (units) *units = least;
+    return best;
+}
+
 // dslash.hip, multi-right-hand-side form (input, output and links of one
-// precision; no subtraction).
+// precision).  sub as in launch_dslash (FP64 only).
 hipError_t launch_dslash_tiled(const OpData& op, int prec, bool dagger, void* out, const void* in, int nrhs,
-                               const LaunchCfg& cfg, hipStream_t s);
+                               const LaunchCfg& cfg, hipStream_t s, const void* sub = nullptr);
+// Launch shape of nrhs right-hand sides when the caller names none (rhs_tile
+// 1: one workgroup per block and right-hand side, the untiled kernel).
+LaunchCfg dslash_default_cfg(const Geom& g, int prec, int nrhs);
+// Units (tile_for's model) of the tiled launch at rhs_tile t.
+double dslash_tile_units(const Geom& g, int prec, int nrhs, int t);
 
 // The same batched launch from FP32 input (FP32 links) into FP16 or BF16
 // output with a per-site scale (the 16-bit Krylov basis of the outer solver).
@@ -455,6 +483,12 @@ enum { BLOCK_MR = 0, BLOCK_JACOBI = 1, BLOCK_EO = 2 };
 hipError_t launch_sap_halfsweep(const OpData& op, int prec, int colour, int n_block, int mode,
                                 void* x, const void* b, int nrhs, const LaunchCfg& cfg, hipStream_t s,
                                 int block_solver = BLOCK_MR);
+// Launch shape of nrhs right-hand sides when the caller names none, and the
+// lanes per site it implies for any tile.
+LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver);
+int sap_default_lanes(const Geom& g, int prec, int nrhs, int block_solver);
+// Units (tile_for's model) of a half-sweep with that tile and those lanes.
+double sap_tile_units(const Geom& g, int nrhs, int t, int lanes);
 // sap_pair.hip: the same half-sweep with two lanes per site (FP32, FP16, BF16).
 hipError_t launch_sap_pair(const OpData& op, int prec, int colour, int n_block, int mode, void* x,
                            const void* b, int nrhs, const LaunchCfg& cfg, hipStream_t s, int block_solver);

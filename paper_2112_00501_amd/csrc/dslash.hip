@@ -246,12 +246,12 @@ __device__ __forceinline__ void hopping_sum_rolled2(const Geom& g, const BlockPo
     }
 }
 
-template <int PIN, int POUT, int PLINK, bool DAG>
+template <int PIN, int POUT, int PLINK, bool DAG, bool SUB>
 __global__ CS_DSLASH_BOUNDS void k_dslash_tiled(Geom g, const void* __restrict__ links,
                                                 const void* __restrict__ clover, double kappa,
                                                 void* __restrict__ out, const void* __restrict__ in,
-                                                size_t in_stride, size_t out_stride, int nrhs, int tile,
-                                                int nitems) {
+                                                const void* __restrict__ sub, size_t in_stride,
+                                                size_t out_stride, int nrhs, int tile, int nitems) {
     using R = typename Arith<PIN>::R;
     using RS = typename LinkIO<PLINK>::R;
     __shared__ lds_cpx<RS> s_lk[4][6][BLOCK_SITES];
@@ -284,8 +284,14 @@ __global__ CS_DSLASH_BOUNDS void k_dslash_tiled(Geom g, const void* __restrict__
             if (DAG) negate_lower(res);
             using RO = typename SpinorIO<POUT>::R;
             cpx<RO> o[12];
+            if constexpr (SUB) {
+                SpinorIO<POUT>::load((const char*)sub + (size_t)r * out_stride, g.nblk, blk, l, o);
 #pragma unroll
-            for (int i = 0; i < 12; ++i) o[i] = {(RO)res[i].re, (RO)res[i].im};
+                for (int i = 0; i < 12; ++i) o[i] = {o[i].re - (RO)res[i].re, o[i].im - (RO)res[i].im};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 12; ++i) o[i] = {(RO)res[i].re, (RO)res[i].im};
+            }
             SpinorIO<POUT>::store((char*)out + (size_t)r * out_stride, g.nblk, blk, l, o);
         };
         int r = r0;
@@ -316,19 +322,29 @@ __global__ CS_DSLASH_BOUNDS void k_dslash_tiled(Geom g, const void* __restrict__
 
 template <int PIN, int POUT, int PLINK>
 hipError_t launch_tiled(const OpData& op, bool dagger, void* out, const void* in, int nrhs,
-                        const LaunchCfg& cfg, hipStream_t s) {
+                        const LaunchCfg& cfg, hipStream_t s, const void* sub = nullptr) {
     const int tile = cfg.rhs_tile > nrhs ? nrhs : cfg.rhs_tile;
     const int nitems = op.g.nblk * ((nrhs + tile - 1) / tile);
     const int grid = cfg.persistent_wgs > 0 && cfg.persistent_wgs < nitems ? cfg.persistent_wgs : nitems;
     const size_t is = spinor_bytes_per_site(PIN) * op.g.V, os = spinor_bytes_per_site(POUT) * op.g.V;
     const void* cl = PIN == P_F64 ? op.clover64 : op.clover32;
     const void* lk = op.links[PLINK];
-    if (dagger)
-        hipLaunchKernelGGL((k_dslash_tiled<PIN, POUT, PLINK, true>), dim3(grid), dim3(BLOCK_SITES), 0, s, op.g, lk, cl,
-                           op.kappa, out, in, is, os, nrhs, tile, nitems);
-    else
-        hipLaunchKernelGGL((k_dslash_tiled<PIN, POUT, PLINK, false>), dim3(grid), dim3(BLOCK_SITES), 0, s, op.g, lk, cl,
-                           op.kappa, out, in, is, os, nrhs, tile, nitems);
+    auto go = [&](auto dag, auto with_sub) {
+        hipLaunchKernelGGL((k_dslash_tiled<PIN, POUT, PLINK, decltype(dag)::value, decltype(with_sub)::value>),
+                           dim3(grid), dim3(BLOCK_SITES), 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os, nrhs,
+                           tile, nitems);
+    };
+    if (sub) {
+        if constexpr (PIN == P_F64 && POUT == P_F64) {
+            if (dagger) go(std::true_type{}, std::true_type{});
+            else go(std::false_type{}, std::true_type{});
+        } else {
+            return hipErrorInvalidValue;
+        }
+    } else {
+        if (dagger) go(std::true_type{}, std::false_type{});
+        else go(std::false_type{}, std::false_type{});
+    }
     return hipGetLastError();
 }
 
@@ -363,11 +379,49 @@ hipError_t launch3(const OpData& op, bool dagger, void* out, const void* in, con
 
 }  // namespace
 
+// The tiled kernel against the one with a workgroup per block and right-hand
+// side, in tile_for's units: workgroups resident at a time (LDS: the tile's
+// links in FP64 or FP32), the load of a tile's links and clover term, and what
+// a full round of the untiled kernel takes.  Fitted at 8^4 to 24^3 x 48 with 2
+// to 16 right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.
+// One round or less of the untiled kernel has no right-hand side to gain by
+// sharing (8^4 with 12: 14 us untiled, 16 in tiles of two).
+struct DslashModel {
+    int slots;
+    double head;
+    int untiled_slots;
+    double untiled_units;
+};
+static DslashModel dslash_model(int prec) {
+    if (prec == P_F64) return {256, 0.5, 256, 1.56};
+    return {512, 1.0, 1024, prec == P_F32 ? 3.7 : 2.8};
+}
+
+double dslash_tile_units(const Geom& g, int prec, int nrhs, int t) {
+    const DslashModel m = dslash_model(prec);
+    if (t <= 1) return (double)(((long long)g.nblk * nrhs + m.untiled_slots - 1) / m.untiled_slots) * m.untiled_units;
+    const long long wgs = (long long)g.nblk * ((nrhs + t - 1) / t);
+    return (double)((wgs + m.slots - 1) / m.slots) * (m.head + t);
+}
+
+LaunchCfg dslash_default_cfg(const Geom& g, int prec, int nrhs) {
+    LaunchCfg c;
+    const DslashModel m = dslash_model(prec);
+    if (nrhs < 2 || (long long)g.nblk * nrhs <= 512) return c;
+    double units;
+    const int t = tile_for(g.nblk, nrhs, m.slots, m.head, &units);
+    // a margin for what the model leaves out (odd tiles: their last right-hand
+    // side goes alone; 945 blocks with three in FP16: 83 us untiled, 84 tiled)
+    if (t > 1 && units < 0.85 * dslash_tile_units(g, prec, nrhs, 1)) c.rhs_tile = t;
+    return c;
+}
+
 hipError_t launch_dslash_tiled(const OpData& op, int prec, bool dagger, void* out, const void* in, int nrhs,
-                               const LaunchCfg& cfg, hipStream_t s) {
+                               const LaunchCfg& cfg, hipStream_t s, const void* sub) {
     ProfScope ps("dslash", s);
+    if (sub && prec != P_F64) return hipErrorInvalidValue;
     switch (prec) {
-    case P_F64: return launch_tiled<P_F64, P_F64, P_F64>(op, dagger, out, in, nrhs, cfg, s);
+    case P_F64: return launch_tiled<P_F64, P_F64, P_F64>(op, dagger, out, in, nrhs, cfg, s, sub);
     case P_F32: return launch_tiled<P_F32, P_F32, P_F32>(op, dagger, out, in, nrhs, cfg, s);
     case P_F16: return launch_tiled<P_F16, P_F16, P_F16>(op, dagger, out, in, nrhs, cfg, s);
     case P_BF16: return launch_tiled<P_BF16, P_BF16, P_BF16>(op, dagger, out, in, nrhs, cfg, s);

@@ -167,6 +167,13 @@ struct Solver {
         return w.host_tail + (k & 1) * n;
     }
 
+    // r = rhs - D x for all right-hand sides (FP64)
+    hipError_t residual(void* r, const void* x, const void* rhs) {
+        const LaunchCfg c = dslash_default_cfg(op.g, P_F64, n);
+        if (c.rhs_tile > 1) return launch_dslash_tiled(op, P_F64, false, r, x, n, c, s, rhs);
+        return launch_dslash(op, P_F64, P_F64, P_F64, false, r, x, rhs, n, s);
+    }
+
     // w = D z for all right-hand sides
     hipError_t apply_w(void* wk, const void* zk) {
         if (w.basis == P_F16 || w.basis == P_BF16) {
@@ -293,7 +300,7 @@ hipError_t gcr_solve(const OpData& op, const GcrParams& p, GcrWork& w, void* x, 
     b_slot1.tail = w.host_tail + n;
     b_slot0.tail = w.host_tail;
     GCR_CHK(blas_norm_to_scalars(b_slot1, rhs, -1, nullptr, s));
-    GCR_CHK(launch_dslash(op, P_F64, P_F64, P_F64, false, w.r, x, rhs, n, s));
+    GCR_CHK(S.residual(w.r, x, rhs));
     GCR_CHK(blas_norm_to_scalars(b_slot0, w.r, S.lo_prec(), w.rlo, s));
     GCR_CHK(hipStreamSynchronize(s));
     for (int r = 0; r < n; ++r) {
@@ -316,7 +323,7 @@ hipError_t gcr_solve(const OpData& op, const GcrParams& p, GcrWork& w, void* x, 
     };
     auto true_residual = [&]() -> hipError_t {
         GCR_CHK(S.upload_mask(not_done()));
-        GCR_CHK(launch_dslash(op, P_F64, P_F64, P_F64, false, w.r, x, rhs, n, s));
+        GCR_CHK(S.residual(w.r, x, rhs));
         BlasCtx bh = S.bc;
         bh.tail = w.host_tail;  // the norm lands in pinned slot 0
         // The smoother's copy is r / |r| with this norm, written once the

@@ -31,8 +31,9 @@ namespace {
     } while (0)
 
 // n_cy SAP cycles on D x = b for nrhs FP32 fields; x0_zero: x starts at zero
-hipError_t sap_cycles(const OpData& op, const LaunchCfg& cfg, int n_cy, int n_mr, bool x0_zero, void* x,
-                      const void* b, int nrhs, hipStream_t s) {
+hipError_t sap_cycles(const OpData& op, int n_cy, int n_mr, bool x0_zero, void* x, const void* b, int nrhs,
+                      hipStream_t s) {
+    const LaunchCfg cfg = sap_default_cfg(op.g, P_F32, nrhs, BLOCK_MR);
     for (int cy = 0; cy < n_cy; ++cy)
         for (int col = 0; col < 2; ++col) {
             const int mode = (x0_zero && cy == 0) ? (col == 0 ? 1 : 2) : 0;
@@ -153,14 +154,14 @@ hipError_t adaptive_pass(const OpData& op, MgData& m, const PassWork& w, hipStre
         done = to;
     }
     MG_CHK(mg_prolong_many(m.g, m.transfer(), nv, cv.x, cv.rs, nv, w.W, s));
-    MG_CHK(sap_cycles(op, m.sap_cfg, m.p.n_cy_post, m.p.n_mr, false, w.W, m.V, nv, s));
+    MG_CHK(sap_cycles(op, m.p.n_cy_post, m.p.n_mr, false, w.W, m.V, nv, s));
     return hipMemcpyAsync(m.V, w.W, m.field_bytes() * nv, hipMemcpyDeviceToDevice, s);
 }
 
 }  // namespace
 
 hipError_t mg_setup(const OpData& op, MgData& m, const void* etas, hipStream_t s) {
-    MG_CHK(sap_cycles(op, m.sap_cfg, m.p.n_cy_setup, m.p.n_mr, true, m.V, etas, m.p.nv, s));
+    MG_CHK(sap_cycles(op, m.p.n_cy_setup, m.p.n_mr, true, m.V, etas, m.p.nv, s));
     MG_CHK(rebuild(op, m, s));
     if (m.p.n_adapt <= 0) return hipSuccess;
     // the workspace of the batched passes is given back once they are done
@@ -234,7 +235,7 @@ hipError_t mg_coarse_phase(const MgData& m, const void* r, hipStream_t s, bool u
 
 hipError_t mg_finish(const OpData& op, const MgData& m, void* z, const void* r, hipStream_t s) {
     MG_CHK(mg_prolong(m.g, m.transfer(), m.p.nv, m.cv.x, z, s));
-    return sap_cycles(op, m.sap_cfg, m.p.n_cy_post, m.p.n_mr, false, z, r, 1, s);
+    return sap_cycles(op, m.p.n_cy_post, m.p.n_mr, false, z, r, 1, s);
 }
 
 hipError_t mg_apply(const OpData& op, const MgData& m, void* z, const void* r, hipStream_t s) {

@@ -95,7 +95,6 @@ struct MgData {
     CbVecs cv{};
     CbScalars* sc = nullptr;
     CbPartials pa{};
-    LaunchCfg sap_cfg{};
     CbScalars* host_sc = nullptr;  // pinned copies of the scalars (stop flags) of up to nv solves
     unsigned long long id = 0; // distinct for every allocation (keys of captured graphs)
     // captured graphs of the coarse phase, one set per input field `r`:

@@ -753,13 +753,43 @@ hipError_t launch_p(const OpData& op, int colour, int n_mr, int mode, void* x, c
 
 }  // namespace
 
-// Lanes per site when the caller leaves the choice to the library.  The
-// lane-pair kernel halves the dependent arithmetic of a block visit but fits
-// one workgroup per compute unit (the one-lane kernel fits two), so it pays
-// only while a colour has at most one block per compute unit (256 on
-// MI355X): measured 7-10% faster at 128 and 256 blocks per colour, 35%
-// slower at 1296 and 4096.
+// Lanes per site when the caller leaves the choice to the library and the
+// launch shape is not chosen for a batch.  The lane-pair kernel halves the
+// dependent arithmetic of a block visit but fits one workgroup per compute
+// unit (the one-lane kernel fits two), so it pays only while a colour has at
+// most one block per compute unit (256 on MI355X): measured 7-10% faster at
+// 128 and 256 blocks per colour, 35% slower at 1296 and 4096.
 static int default_lanes_per_site(const Geom& g) { return g.nblk / 2 <= 256 ? 2 : 1; }
+
+// For a batch the line lies at 256 visits of a colour in all (blocks times
+// right-hand sides): at 16^3 x 32 one right-hand side takes 107 us a cycle pair
+// with lane pairs and 118 with one lane, two take 200 and 163, twelve 891 and
+// 687 in their best tiles.
+int sap_default_lanes(const Geom& g, int prec, int nrhs, int block_solver) {
+    if (prec == P_F64 || block_solver == BLOCK_EO) return 1;
+    return (long long)(g.nblk / 2) * nrhs <= 256 ? 2 : 1;
+}
+
+// Workgroups resident at a time and the cost of a tile's links and clover
+// term in units of one visit, fitted to sweeps of the tile at 16^3 x 32 and
+// 24^3 x 48.
+constexpr int SAP_SLOTS[3] = {0, 512, 256};  // by lanes per site
+constexpr double SAP_HEAD = 0.35;
+
+double sap_tile_units(const Geom& g, int nrhs, int t, int lanes) {
+    const long long wgs = (long long)(g.nblk / 2) * ((nrhs + t - 1) / t);
+    return (double)((wgs + SAP_SLOTS[lanes] - 1) / SAP_SLOTS[lanes]) * (SAP_HEAD + t);
+}
+
+LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver) {
+    LaunchCfg c;
+    c.lanes_per_site = sap_default_lanes(g, prec, nrhs, block_solver);
+    // the FP64 kernel keeps nothing of the block between right-hand sides, and
+    // the even-odd one is bound by its arithmetic with one workgroup per unit
+    if (nrhs > 1 && prec != P_F64 && block_solver != BLOCK_EO)
+        c.rhs_tile = tile_for(g.nblk / 2, nrhs, SAP_SLOTS[c.lanes_per_site], SAP_HEAD, nullptr);
+    return c;
+}
 
 hipError_t launch_sap_halfsweep(const OpData& op, int prec, int colour, int n_mr, int mode, void* x,
                                 const void* b, int nrhs, const LaunchCfg& cfg, hipStream_t s, int bs) {
