@@ -40,10 +40,8 @@ constexpr int BLOCK_SITES = 256;  // one 4^4 block = one workgroup
 // operator and smoother kernels (0 = compiler default); XCD-aware ordering of
 // workgroups; non-temporal loads of the fields that are read exactly once
 // (links, clover) and non-temporal stores of FP32 spinor fields, which keeps
-// the caches for the face neighbours that are read twice; the operator's
-// hopping sum as a rolled loop (bounded registers, 4 waves per SIMD) instead
-// of fully unrolled; a raised wave priority during the loads of a SAP block
-// visit.
+// the caches for the face neighbours that are read twice; a raised wave
+// priority during the loads of a SAP block visit.
 #ifndef CS_DSLASH_WAVES
 #define CS_DSLASH_WAVES 0
 #endif
@@ -58,14 +56,6 @@ constexpr int BLOCK_SITES = 256;  // one 4^4 block = one workgroup
 #endif
 #ifndef CS_NT_STORES
 #define CS_NT_STORES 1
-#endif
-#ifndef CS_DSLASH_ROLLED
-#define CS_DSLASH_ROLLED 1
-#endif
-// Float-arithmetic operator: 0 = every neighbour read through the caches,
-// 1 = the block's spinor staged in LDS, 2 = its spinor and links staged.
-#ifndef CS_DSLASH_STAGED
-#define CS_DSLASH_STAGED 1
 #endif
 #ifndef CS_BLOCK_ORDER_TZ
 #define CS_BLOCK_ORDER_TZ 2
@@ -439,17 +429,18 @@ struct LaunchCfg {
 // Tile of right-hand sides for a launch over `blocks` blocks with `slots`
 // workgroups on the GPU at a time, from a model that the measured times follow
 // to about 5 %: a workgroup takes head + tile units (head: what it loads once
-// for its tile), and the launch as many rounds as the slots need for all
+// for its tile; odd: what an odd tile costs on top where right-hand sides go
+// in pairs), and the launch as many rounds as the slots need for all
 // workgroups, so a tile that leaves a round nearly empty loses to one that
 // fills it (12 right-hand sides of 512 blocks in 512 slots: tiles of 4 and 8
-// take 137 and 154 us for the FP32 operator, 6 and 12 take 127 and 118).
+// take 135 and 153 us for the FP32 operator, 6 and 12 take 125 and 117).
 // *units: the model's time.
-inline int tile_for(long long blocks, int nrhs, int slots, double head, double* units) {
+inline int tile_for(long long blocks, int nrhs, int slots, double head, double odd, double* units) {
     int best = 1;
     double least = 0;
     for (int t = 1; t <= nrhs && t <= 64; ++t) {
         const long long wgs = blocks * ((nrhs + t - 1) / t);
-        const double u = (double)((wgs + slots - 1) / slots) * (head + t);
+        const double u = (double)((wgs + slots - 1) / slots) * (head + t + (t & 1 ? odd : 0.0));
         if (t == 1 || u < least) {
             least = u;
             best = t;

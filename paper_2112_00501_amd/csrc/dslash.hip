@@ -6,11 +6,149 @@
 // kernel is bound by HBM bandwidth: per site it reads the spinor (the eight
 // neighbours come from cache), four compressed links (the backward links are
 // the neighbours' forward links) and the clover term, and writes one spinor.
+#include <type_traits>
+
 #include "dslash_core.hpp"
 
 namespace cs {
 
 namespace {
+
+// The hopping sum with the loads of AHEAD hops in flight while a hop is
+// computed, as straight code: for launches of few workgroups, whose time is
+// the chain of one workgroup's loads.  The same terms in the same order as
+// hopping_sum_rolled.  A fetched hop is kept as loaded (16-bit words packed,
+// third link row not yet rebuilt), so that nothing waits for it before its
+// turn.
+template <int P>
+struct RawSpinor {  // FP64, FP32
+    using R = typename SpinorIO<P>::R;
+    cpx<R> c[12];
+    __device__ __forceinline__ void load(const void* base, int nblk, int blk, int l) {
+        SpinorIO<P>::load(base, nblk, blk, l, c);
+    }
+    __device__ __forceinline__ void get(cpx<R>* o) const {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) o[k] = c[k];
+    }
+};
+template <int P>
+struct RawSpinor16 {
+    typename SpinorIO16<P>::Raw r;
+    __device__ __forceinline__ void load(const void* base, int nblk, int blk, int l) {
+        SpinorIO16<P>::load_raw(base, nblk, blk, l, r);
+    }
+    __device__ __forceinline__ void get(cpx<float>* o) const {
+        SpinorIO16<P>::unpack(r, o);
+        keep_rounding(o);
+    }
+};
+template <>
+struct RawSpinor<P_F16> : RawSpinor16<P_F16> {};
+template <>
+struct RawSpinor<P_BF16> : RawSpinor16<P_BF16> {};
+
+template <int P>
+struct RawLink {  // FP64, FP32
+    using R = typename LinkIO<P>::R;
+    cpx<R> u[6];
+    __device__ __forceinline__ void load(const void* base, int blk, int l, int mu) {
+        LinkIO<P>::template load6<false>(base, blk, l, mu, u);
+    }
+    __device__ __forceinline__ void get(cpx<R>* o) const {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) o[k] = u[k];
+    }
+};
+template <int P>
+struct RawLink16 {
+    uint2 w[3];
+    __device__ __forceinline__ void load(const void* base, int blk, int l, int mu) {
+        const uint2* p = (const uint2*)base + ((size_t)blk * 4 + mu) * 3 * BLOCK_SITES + l;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k] = p[k * BLOCK_SITES];
+    }
+    __device__ __forceinline__ void get(cpx<float>* o) const {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            unpack2<P>(w[k].x, o[2 * k].re, o[2 * k].im);
+            unpack2<P>(w[k].y, o[2 * k + 1].re, o[2 * k + 1].im);
+        }
+    }
+};
+template <>
+struct RawLink<P_F16> : RawLink16<P_F16> {};
+template <>
+struct RawLink<P_BF16> : RawLink16<P_BF16> {};
+
+template <int PIN, int PLINK>
+struct RawHop {
+    RawSpinor<PIN> psi;
+    RawLink<PLINK> link;
+    template <int H>
+    __device__ __forceinline__ void load(const Geom& g, const BlockPos& p, int l, const void* in, const void* links) {
+        constexpr int MU = H >> 1, DIR = (H & 1) ? -1 : +1;
+        int nl;
+        bool inside;
+        const int nb = neighbour(g, p, l, MU, DIR, &nl, &inside);
+        psi.load(in, g.nblk, nb, nl);
+        link.load(links, DIR > 0 ? p.blk : nb, DIR > 0 ? l : nl, MU);
+    }
+    template <int H, bool DAG, typename R>
+    __device__ __forceinline__ void apply(const Geom& g, const BlockPos& p, int l, cpx<R>* acc) const {
+        constexpr int MU = H >> 1, DIR = (H & 1) ? -1 : +1, lc = DIR > 0 ? 3 : 0;
+        cpx<R> c[12], u[9];
+        psi.get(c);
+        link.get(u);
+        if (DAG) negate_lower(c);
+        if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, DIR, ((l >> 6) & 3) != lc), &c[0].re, 24);
+        su3_row2(u);
+        hop_term<MU, -DIR>(u, c, acc);
+    }
+};
+
+template <int H, int AHEAD, bool DAG, typename HOP, typename R>
+__device__ __forceinline__ void hops_ahead(const Geom& g, const BlockPos& p, int l, const void* in,
+                                           const void* links, HOP* f, cpx<R>* acc) {
+    if constexpr (H < 8) {
+        constexpr int N = AHEAD + 1;
+        if constexpr (H + AHEAD < 8) f[(H + AHEAD) % N].template load<H + AHEAD>(g, p, l, in, links);
+        // the fetch stays before this hop's arithmetic and the arithmetic here,
+        // or the compiler would issue all loads first and spill
+        __builtin_amdgcn_sched_barrier(0);
+        f[H % N].template apply<H, DAG>(g, p, l, acc);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(acc[k].re), "+v"(acc[k].im));
+        __builtin_amdgcn_sched_barrier(0);
+        hops_ahead<H + 1, AHEAD, DAG>(g, p, l, in, links, f, acc);
+    }
+}
+
+template <int PIN, int PLINK, int AHEAD, bool DAG, typename R>
+__device__ __forceinline__ void hopping_sum_ahead(const Geom& g, const BlockPos& p, int l, const void* in,
+                                                  const void* links, cpx<R>* acc) {
+    static_assert(AHEAD >= 1 && AHEAD <= 5, "the first hops fetched here");
+    RawHop<PIN, PLINK> f[AHEAD + 1];
+    f[0].template load<0>(g, p, l, in, links);
+    if constexpr (AHEAD > 1) f[1].template load<1>(g, p, l, in, links);
+    if constexpr (AHEAD > 2) f[2].template load<2>(g, p, l, in, links);
+    if constexpr (AHEAD > 3) f[3].template load<3>(g, p, l, in, links);
+    if constexpr (AHEAD > 4) f[4].template load<4>(g, p, l, in, links);
+    hops_ahead<0, AHEAD, DAG>(g, p, l, in, links, f, acc);
+}
+
+// One right-hand side per workgroup.  Bound by HBM on large lattices (per
+// site the FP32 operator cannot do without 672 bytes: 32^3 x 64 takes 300 us,
+// 4.7 TB/s of them, with 1.27 times as many crossing the L2) and by the chain
+// of loads on small ones, where a launch is a round or two of workgroups.
+// With the loop over hops not unrolled every hop waited for its own loads:
+// 13.3 us at 8^4 in FP64 and 13.1 in FP32 against 9.9 and 7.8 now, 47 and 21.6
+// against 33 and 18.4 at 16^3 x 32, 719 against 614 for FP64 at 32^3 x 64.
+// Hops in flight: two in FP64, three below, measured best of 1-3 and 2-5 on
+// lattices of 512 blocks and more (registers: two waves per SIMD in FP32, four
+// in the 16-bit formats).
+template <int P>
+constexpr int hops_in_flight() { return P == P_F64 ? 2 : 3; }
 
 template <int PIN, int POUT, int PLINK, bool DAG, bool SUB>
 __global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links,
@@ -27,11 +165,9 @@ __global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links
     cpx<R> acc[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = {(R)0, (R)0};
-    GlobalSpinor<PIN, DAG> ld{src, g.nblk};
-    GlobalLinks<PLINK> lk{links};
-    if (CS_DSLASH_ROLLED || PIN == P_F64) hopping_sum_rolled<R>(g, p, l, ld, lk, acc);
-    else hopping_sum<R>(g, p, l, ld, lk, acc);
+    hopping_sum_ahead<PIN, PLINK, hops_in_flight<PIN>(), DAG>(g, p, l, src, links, acc);
 
+    GlobalSpinor<PIN, DAG> ld{src, g.nblk};
     cpx<R> self[12], res[12];
     ld.load(blk, l, self);
     R cl[72];
@@ -54,134 +190,11 @@ __global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links
     SpinorIO<POUT>::store((char*)out + r * out_stride, g.nblk, blk, l, o);
 }
 
-// Staged form of the same operator (float arithmetic): the block's input
-// spinor is copied to LDS once (converted to float, with the gamma5 sign of
-// D^dag applied), and every in-block hop reads its neighbour from there;
-// only the hops that leave the block read HBM.  With LINKS_LDS the block's
-// links (rows 0 and 1) are staged too, so the backward hops inside the block
-// take the neighbour lane's link from LDS instead of re-reading it.  Each
-// spinor and link word of the block is then fetched from HBM once by its own
-// workgroup; the plain kernel above fetches each spinor once per hop and
-// relies on the caches for the reuse.
-template <int P, bool DAG>
-struct StagedSpinor {
-    const lds_cpx<float> (*s)[BLOCK_SITES];
-    const void* base;
-    int nblk;
-    __device__ __forceinline__ bool want(bool) const { return true; }
-    template <typename R>
-    __device__ __forceinline__ void load_nb(int blk, int l, bool inside, cpx<R>* c) const {
-        if (inside) {
-#pragma unroll
-            for (int k = 0; k < 12; ++k) c[k] = {(R)s[k][l].re, (R)s[k][l].im};
-        } else {
-            using RS = typename SpinorIO<P>::R;
-            cpx<RS> t[12];
-            SpinorIO<P>::load(base, nblk, blk, l, t);
-#pragma unroll
-            for (int k = 0; k < 12; ++k) c[k] = {(R)t[k].re, (R)t[k].im};
-            if (DAG) negate_lower(c);
-        }
-    }
-};
-
-template <int PLINK>
-struct StagedLinks {
-    const lds_cpx<float> (*sm)[6][BLOCK_SITES];
-    const void* base;
-    template <typename R>
-    __device__ __forceinline__ void load(int blk, int l, int mu, bool inside, cpx<R>* u) const {
-        if (inside) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) u[k] = {(R)sm[mu][k][l].re, (R)sm[mu][k][l].im};
-            su3_row2(u);
-        } else {
-            load_link<PLINK, R, false>(base, blk, l, mu, u);
-        }
-    }
-};
-
-template <bool ON>
-struct StagedLinkSmem { lds_cpx<float> u[4][6][BLOCK_SITES]; };
-template <>
-struct StagedLinkSmem<false> { lds_cpx<float> u[1][6][1]; };
-
-template <int PIN, int POUT, int PLINK, bool DAG, bool SUB, bool LINKS_LDS>
-__global__ CS_DSLASH_BOUNDS void k_dslash_staged(Geom g, const void* __restrict__ links,
-                                                 const void* __restrict__ clover, float kappa,
-                                                 void* __restrict__ out, const void* __restrict__ in,
-                                                 const void* __restrict__ sub, size_t in_stride,
-                                                 size_t out_stride) {
-    __shared__ lds_cpx<float> s_psi[12][BLOCK_SITES];
-    __shared__ StagedLinkSmem<LINKS_LDS> s_lk;
-    const int blk = block_of_item(g, xcd_remap(blockIdx.x, g.nblk)), l = threadIdx.x, r = blockIdx.y;
-    const char* src = (const char*)in + r * in_stride;
-    const BlockPos p = block_pos(g, blk);
-
-    {
-        using RS = typename SpinorIO<PIN>::R;
-        cpx<RS> t[12];
-        SpinorIO<PIN>::load(src, g.nblk, blk, l, t);
-        cpx<float> v[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) v[k] = {(float)t[k].re, (float)t[k].im};
-        if (DAG) negate_lower(v);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) s_psi[k][l].set(v[k]);
-    }
-    if constexpr (LINKS_LDS) {
-        for (int mu = 0; mu < 4; ++mu) {
-            cpx<typename LinkIO<PLINK>::R> u[6];
-            LinkIO<PLINK>::load6(links, blk, l, mu, u);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) s_lk.u[mu][k][l] = {(float)u[k].re, (float)u[k].im};
-        }
-    }
-    __syncthreads();
-
-    cpx<float> acc[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = {0.f, 0.f};
-    StagedSpinor<PIN, DAG> ls{s_psi, src, g.nblk};
-    if constexpr (LINKS_LDS) {
-        StagedLinks<PLINK> lk{s_lk.u, links};
-        hopping_sum_rolled<float>(g, p, l, ls, lk, acc);
-    } else {
-        GlobalLinks<PLINK, false> lk{links};
-        hopping_sum_rolled<float>(g, p, l, ls, lk, acc);
-    }
-
-    cpx<float> self[12], res[12];
-    ls.load_nb(blk, l, true, self);
-    float cl[72];
-    CloverIO<float>::load(clover, blk, l, cl);
-    clover_apply(cl, self, res);
-#pragma unroll
-    for (int i = 0; i < 12; ++i) res[i] = {res[i].re - kappa * acc[i].re, res[i].im - kappa * acc[i].im};
-    if (DAG) negate_lower(res);
-    using RO = typename SpinorIO<POUT>::R;
-    cpx<RO> o[12];
-    if (SUB) {
-        SpinorIO<POUT>::load((const char*)sub + r * out_stride, g.nblk, blk, l, o);
-#pragma unroll
-        for (int i = 0; i < 12; ++i) o[i] = {o[i].re - (RO)res[i].re, o[i].im - (RO)res[i].im};
-    } else {
-#pragma unroll
-        for (int i = 0; i < 12; ++i) o[i] = {(RO)res[i].re, (RO)res[i].im};
-    }
-    SpinorIO<POUT>::store((char*)out + r * out_stride, g.nblk, blk, l, o);
-}
-
 // Multi-right-hand-side variant: work item = (block, tile of right-hand
 // sides).  The block's links go to LDS once and its clover term to registers
 // once per item; every right-hand side of the tile reuses them.  Backward
 // links of neighbours outside the block come from HBM (cache).  With
 // gridDim.x < nitems the workgroups stride over the items (persistent).
-template <bool ON>
-struct DLinkSmem { lds_cpx<float> u[4][6][BLOCK_SITES]; };
-template <>
-struct DLinkSmem<false> { lds_cpx<double> u[4][6][BLOCK_SITES]; };
-
 template <typename RS, int PLINK>
 struct MixedLinks {
     const lds_cpx<RS> (*sm)[6][BLOCK_SITES];
@@ -351,28 +364,19 @@ hipError_t launch_tiled(const OpData& op, bool dagger, void* out, const void* in
 template <int PIN, int POUT, int PLINK>
 hipError_t launch3(const OpData& op, bool dagger, void* out, const void* in, const void* sub,
                    int nrhs, hipStream_t s) {
-    const dim3 grid(op.g.nblk, nrhs), block(BLOCK_SITES);
     const size_t is = spinor_bytes_per_site(PIN) * op.g.V, os = spinor_bytes_per_site(POUT) * op.g.V;
     const void* cl = PIN == P_F64 ? op.clover64 : op.clover32;
-    const void* lk = op.links[PLINK];
-    if constexpr (PIN != P_F64 && CS_DSLASH_STAGED) {
-        constexpr bool LL = CS_DSLASH_STAGED == 2;
-        const float k = (float)op.kappa;
-        if (dagger) {
-            if (sub) hipLaunchKernelGGL((k_dslash_staged<PIN, POUT, PLINK, true, true, LL>), grid, block, 0, s, op.g, lk, cl, k, out, in, sub, is, os);
-            else hipLaunchKernelGGL((k_dslash_staged<PIN, POUT, PLINK, true, false, LL>), grid, block, 0, s, op.g, lk, cl, k, out, in, sub, is, os);
-        } else {
-            if (sub) hipLaunchKernelGGL((k_dslash_staged<PIN, POUT, PLINK, false, true, LL>), grid, block, 0, s, op.g, lk, cl, k, out, in, sub, is, os);
-            else hipLaunchKernelGGL((k_dslash_staged<PIN, POUT, PLINK, false, false, LL>), grid, block, 0, s, op.g, lk, cl, k, out, in, sub, is, os);
-        }
-        return hipGetLastError();
-    }
+    auto go = [&](auto dag, auto with_sub) {
+        hipLaunchKernelGGL((k_dslash<PIN, POUT, PLINK, decltype(dag)::value, decltype(with_sub)::value>),
+                           dim3(op.g.nblk, nrhs), dim3(BLOCK_SITES), 0, s, op.g, op.links[PLINK], cl, op.kappa, out,
+                           in, sub, is, os);
+    };
     if (dagger) {
-        if (sub) hipLaunchKernelGGL((k_dslash<PIN, POUT, PLINK, true, true>), grid, block, 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os);
-        else hipLaunchKernelGGL((k_dslash<PIN, POUT, PLINK, true, false>), grid, block, 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os);
+        if (sub) go(std::true_type{}, std::true_type{});
+        else go(std::true_type{}, std::false_type{});
     } else {
-        if (sub) hipLaunchKernelGGL((k_dslash<PIN, POUT, PLINK, false, true>), grid, block, 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os);
-        else hipLaunchKernelGGL((k_dslash<PIN, POUT, PLINK, false, false>), grid, block, 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os);
+        if (sub) go(std::false_type{}, std::true_type{});
+        else go(std::false_type{}, std::false_type{});
     }
     return hipGetLastError();
 }
@@ -380,39 +384,41 @@ hipError_t launch3(const OpData& op, bool dagger, void* out, const void* in, con
 }  // namespace
 
 // The tiled kernel against the one with a workgroup per block and right-hand
-// side, in tile_for's units: workgroups resident at a time (LDS: the tile's
-// links in FP64 or FP32), the load of a tile's links and clover term, and what
-// a full round of the untiled kernel takes.  Fitted at 8^4 to 24^3 x 48 with 2
-// to 16 right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.
-// One round or less of the untiled kernel has no right-hand side to gain by
-// sharing (8^4 with 12: 14 us untiled, 16 in tiles of two).
+// side, in tile_for's units: workgroups resident at a time, the load of a
+// tile's links and clover term, the cost of an odd tile, and what a full round
+// of the untiled kernel takes.  Fitted at 8^4 to 24^3 x 48 with 2 to 16
+// right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.  In FP64
+// sharing pays where links, clover term and a field leave the 256 MB cache
+// (24^3 x 48 with 12: 2.41 ms untiled, 2.03 in tiles of six; 16^3 x 32 with 5:
+// 151 us untiled, 157 in one tile).  Two workgroups per compute unit or less
+// have nothing to gain by sharing (8^4 with 12: 9 us untiled, 16 in tiles of
+// two).
 struct DslashModel {
     int slots;
-    double head;
+    double head, odd;
     int untiled_slots;
     double untiled_units;
 };
-static DslashModel dslash_model(int prec) {
-    if (prec == P_F64) return {256, 0.5, 256, 1.56};
-    return {512, 1.0, 1024, prec == P_F32 ? 3.7 : 2.8};
+static DslashModel dslash_model(const Geom& g, int prec) {
+    if (prec == P_F64) return {256, 0.5, 0.0, 256, g.V * 1344 > (256ll << 20) ? 1.5 : 1.0};
+    if (prec == P_F32) return {512, 1.0, 0.6, 512, 1.65};
+    return {512, 1.0, 0.8, 1024, 2.45};
 }
 
 double dslash_tile_units(const Geom& g, int prec, int nrhs, int t) {
-    const DslashModel m = dslash_model(prec);
+    const DslashModel m = dslash_model(g, prec);
     if (t <= 1) return (double)(((long long)g.nblk * nrhs + m.untiled_slots - 1) / m.untiled_slots) * m.untiled_units;
     const long long wgs = (long long)g.nblk * ((nrhs + t - 1) / t);
-    return (double)((wgs + m.slots - 1) / m.slots) * (m.head + t);
+    return (double)((wgs + m.slots - 1) / m.slots) * (m.head + t + (t & 1 ? m.odd : 0.0));
 }
 
 LaunchCfg dslash_default_cfg(const Geom& g, int prec, int nrhs) {
     LaunchCfg c;
-    const DslashModel m = dslash_model(prec);
+    const DslashModel m = dslash_model(g, prec);
     if (nrhs < 2 || (long long)g.nblk * nrhs <= 512) return c;
     double units;
-    const int t = tile_for(g.nblk, nrhs, m.slots, m.head, &units);
-    // a margin for what the model leaves out (odd tiles: their last right-hand
-    // side goes alone; 945 blocks with three in FP16: 83 us untiled, 84 tiled)
-    if (t > 1 && units < 0.85 * dslash_tile_units(g, prec, nrhs, 1)) c.rhs_tile = t;
+    const int t = tile_for(g.nblk, nrhs, m.slots, m.head, m.odd, &units);
+    if (t > 1 && units < 0.95 * dslash_tile_units(g, prec, nrhs, 1)) c.rhs_tile = t;
     return c;
 }
 

@@ -8,6 +8,14 @@
 
 namespace cs {
 
+// The 24 reals as they are: 16-bit words times their scale are rounded here
+// and not contracted into the sums they enter, so that the operator's kernels
+// agree bit for bit.
+__device__ __forceinline__ void keep_rounding(cpx<float>* c) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) asm("" : "+v"(c[k].re), "+v"(c[k].im));
+}
+
 // Spinors from HBM; with DAG the lower two spins are negated on load (the
 // gamma5 sandwich of D^dag = gamma5 D gamma5).
 template <int P, bool DAG>
@@ -20,6 +28,7 @@ struct GlobalSpinor {
         using RS = typename SpinorIO<P>::R;
         cpx<RS> t[12];
         SpinorIO<P>::load(base, nblk, blk, l, t);
+        if constexpr (P == P_F16 || P == P_BF16) keep_rounding(t);
 #pragma unroll
         for (int k = 0; k < 12; ++k) c[k] = {(R)t[k].re, (R)t[k].im};
         if (DAG) negate_lower(c);

@@ -158,12 +158,25 @@ struct SpinorIO<P_BF16> : SpinorIO16<P_BF16> {};
 
 // ---------------------------------------------------------------------- links
 
-// Row 2 of an SU(3) matrix from rows 0 and 1: conj(row0 x row1).
+// Row 2 of an SU(3) matrix from rows 0 and 1: conj(row0 x row1).  The
+// roundings are spelled out (one product, then three FMA), so that every
+// kernel rebuilds the same bits whatever the compiler contracts around it.
+template <typename R>
+__device__ __forceinline__ cpx<R> conj_minor(cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d) {  // conj(a b - c d)
+    R re = a.re * b.re, im = -(a.re * b.im);
+    re = fma(-a.im, b.im, re);
+    im = fma(-a.im, b.re, im);
+    re = fma(-c.re, d.re, re);
+    im = fma(c.re, d.im, im);
+    re = fma(c.im, d.im, re);
+    im = fma(c.im, d.re, im);
+    return {re, im};
+}
 template <typename R>
 __device__ __forceinline__ void su3_row2(cpx<R>* u) {
-    u[6] = conj(u[1] * u[5] - u[2] * u[4]);
-    u[7] = conj(u[2] * u[3] - u[0] * u[5]);
-    u[8] = conj(u[0] * u[4] - u[1] * u[3]);
+    u[6] = conj_minor(u[1], u[5], u[2], u[4]);
+    u[7] = conj_minor(u[2], u[3], u[0], u[5]);
+    u[8] = conj_minor(u[0], u[4], u[1], u[3]);
 }
 
 template <int P>
