@@ -99,148 +99,245 @@ __global__ __launch_bounds__(TPB) void k_mg_orthonormalize(Geom g, char* P, size
     }
 }
 
-// Column (chi_c, j) of P on one site: field j with the other chirality zeroed.
-__device__ __forceinline__ void column_site(const char* P, size_t fs, int nv, int col, int nblk, int blk, int l,
-                                            cpx<float>* c) {
-    const int chi = col / nv, j = col % nv;
-    load_f32(P, fs, j, nblk, blk, l, c);
-#pragma unroll
-    for (int k = 0; k < 12; ++k)
-        if ((k < 6 ? 0 : 1) != chi) c[k] = {0.f, 0.f};
-}
-
-struct LdsColumn {  // in-block neighbours for the self term
-    const lds_cpx<float> (*s)[BLOCK_SITES];
-    __device__ __forceinline__ bool want(bool inside) const { return inside; }
-    template <typename R>
-    __device__ __forceinline__ void load_nb(int, int l, bool, cpx<R>* c) const {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) c[k] = s[k][l].get();
-    }
-};
-
 // Assembly of D_c[a][d][col][row] = <p_{a,row}, D p_{n(a,d),col}> restricted
-// to the terms of D that couple aggregate a to its neighbour in direction d.
-// One workgroup per (aggregate, column), lane = site; the nc workgroups of an
-// aggregate are consecutive on one XCD, so the aggregate's rows of P, links
-// and clover term come from HBM once and from that XCD's L2 for the others.
-// The column is applied once: the self term (clover and the in-aggregate
-// hops of the column, staged in LDS) and the four -mu face terms (hops from
-// the neighbouring aggregates) stay in registers while every row of P
-// streams past; per row each lane
-// forms 20 partial dot products (self term and four faces, two row
-// chiralities, re and im), which are summed over the lanes through a
-// lane-major LDS array in a fixed order.  The +mu blocks follow afterwards
-// from gamma5-hermiticity (k_mg_assemble_fwd).
-constexpr int ASM_R = 2;                 // rows per reduction round
-constexpr int ASM_VALS = 20 * ASM_R;     // partial sums per lane and round
-constexpr int ASM_LD = ASM_VALS + 1;     // padded row of the lane-major array
+// to the terms of D that couple aggregate a to its neighbour in direction d
+// (d = 0 and the -mu faces; the +mu blocks follow from gamma5-hermiticity,
+// k_mg_assemble_fwd).
+//
+// Every block of D_c is a contraction over the sites and components of an
+// aggregate (self) or a face, so it runs on the matrix cores in FP32
+// (v_mfma_f32_16x16x4_f32).  A lane of a wave is (column j = lane % 16, site
+// lane / 16 of four): it loads its column's null vector at its site and the
+// neighbours, applies D to the two chirality halves, and then holds exactly
+// the operands of the products, the vector itself as row j of P^dag and D p as
+// column j, for four sites and one component at a time; nothing is transposed
+// or reduced across lanes.  Workgroup = (aggregate, 16 columns j of either
+// chirality): first the self term, one t slice per wave, summed over the waves
+// in LDS; then the faces, wave mu the -mu face.  RT row tiles of 16 cover nv
+// (rows and columns past nv repeat field nv - 1 and are not stored).
+// Per site and column about 1400 VALU instructions apply D and 96 products of
+// 32 cycles contract; with one column per workgroup and dot products reduced
+// through LDS the same work took 17.6 ms at 32^3 x 64 with 16 vectors.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// y += conj(q) . x over the spins of each chirality: out[2 chi + (re, im)]
-__device__ __forceinline__ void chi_dots(const cpx<float>* q, const cpx<float>* x, float* out) {
-    float a[4] = {0.f, 0.f, 0.f, 0.f};
+// y0 += (1 + S gamma_mu) U' psi_0, y1 += (1 + S gamma_mu) U' psi_1 for the
+// chirality halves psi_0 (spins 0, 1) and psi_1 (spins 2, 3) of psi
+template <int MU, int S>
+__device__ __forceinline__ void hop_halves(const cpx<float>* u, const cpx<float>* psi, cpx<float>* y0,
+                                           cpx<float>* y1) {
+    cpx<float> h[6], v[6];
+    su3_mul_half<(S > 0)>(u, psi, v);
+    spin_reconstruct_add<MU, S>(v, y0);
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        const int o = k < 6 ? 0 : 2;
-        a[o] += q[k].re * x[k].re + q[k].im * x[k].im;
-        a[o + 1] += q[k].re * x[k].im - q[k].im * x[k].re;
+    for (int a = 0; a < 3; ++a) {  // S A_mu psi_lo
+        const cpx<float> s2 = psi[6 + a], s3 = psi[9 + a], n2 = {-s2.re, -s2.im}, n3 = {-s3.re, -s3.im};
+        if (MU == 0) {
+            h[a] = S > 0 ? mul_mi(s3) : mul_i(s3);
+            h[3 + a] = S > 0 ? mul_mi(s2) : mul_i(s2);
+        } else if (MU == 1) {
+            h[a] = S > 0 ? n3 : s3;
+            h[3 + a] = S > 0 ? s2 : n2;
+        } else if (MU == 2) {
+            h[a] = S > 0 ? mul_mi(s2) : mul_i(s2);
+            h[3 + a] = S > 0 ? mul_i(s3) : mul_mi(s3);
+        } else {
+            h[a] = S > 0 ? s2 : n2;
+            h[3 + a] = S > 0 ? s3 : n3;
+        }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) out[k] = a[k];
+    su3_mul_half<(S > 0)>(u, h, v);
+    spin_reconstruct_add<MU, S>(v, y1);
 }
 
-// -kappa times the backward hop across the -MU face into lane l (zero on
-// lanes not on that face)
+// The two hops of direction MU inside the aggregate into site l
 template <int MU>
-__device__ __forceinline__ void back_face(const Geom& g, const BlockPos& p, int l, const void* links,
-                                          const char* P, size_t fs, int nv, int col, float kappa, cpx<float>* y) {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) y[k] = {0.f, 0.f};
-    if (((l >> (2 * MU)) & 3) != 0) return;
+__device__ __forceinline__ void hops_inside(int blk, int l, const void* links, const char* Pj, int nblk,
+                                            cpx<float>* y0, cpx<float>* y1) {
+    constexpr int sh = 2 * MU;
+    const int lc = (l >> sh) & 3;
+    if (lc < 3) {
+        cpx<float> psi[12], u[9];
+        SpinorIO<P_F32>::load(Pj, nblk, blk, l + (1 << sh), psi);
+        load_link<P_F32, float, false>(links, blk, l, MU, u);
+        hop_halves<MU, -1>(u, psi, y0, y1);
+    }
+    if (lc > 0) {
+        cpx<float> psi[12], u[9];
+        SpinorIO<P_F32>::load(Pj, nblk, blk, l - (1 << sh), psi);
+        load_link<P_F32, float, false>(links, blk, l - (1 << sh), MU, u);
+        hop_halves<MU, +1>(u, psi, y0, y1);
+    }
+}
+
+// The hop across the -MU face of block p into site l (lc_mu = 0)
+template <int MU>
+__device__ __forceinline__ void hop_back_face(const Geom& g, const BlockPos& p, int l, const void* links,
+                                              const char* Pj, cpx<float>* y0, cpx<float>* y1) {
     int nl;
     bool in;
     const int nb = neighbour(g, p, l, MU, -1, &nl, &in);
     cpx<float> psi[12], u[9];
-    column_site(P, fs, nv, col, g.nblk, nb, nl, psi);
+    SpinorIO<P_F32>::load(Pj, g.nblk, nb, nl, psi);
     if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, -1, in), &psi[0].re, 24);
     load_link<P_F32, float, false>(links, nb, nl, MU, u);  // U_mu(x - mu)
-    hop_term<MU, +1>(u, psi, y);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) y[k] = {-kappa * y[k].re, -kappa * y[k].im};
+    hop_halves<MU, +1>(u, psi, y0, y1);
 }
 
-__global__ __launch_bounds__(TPB, 2) void k_mg_assemble(Geom g, const void* links, const void* clover, float kappa,
-                                                     const char* P, size_t fs, int nv, float2* Dc) {
-    const int l = threadIdx.x, nc = 2 * nv;
-    const int w = xcd_remap(blockIdx.x, g.nblk * nc), blk = w / nc;
-    const BlockPos p = block_pos(g, blk);
-    __shared__ lds_cpx<float> s[12][BLOCK_SITES];
-    __shared__ float red[BLOCK_SITES * ASM_LD];
-    __shared__ float part[ASM_VALS][4];
-    {
-        const int col = w % nc;
-        cpx<float> y0[12], yf[4][12];
-        {
-            cpx<float> c[12], acc[12];
-            column_site(P, fs, nv, col, g.nblk, blk, l, c);
+// Sums of the products of rows and columns: [row chirality][column chirality]
+struct AsmTile {
+    f32x4 re[2][2], im[2][2];
+};
+
+__device__ __forceinline__ void asm_clear(AsmTile& t) {
 #pragma unroll
-            for (int k = 0; k < 12; ++k) s[k][l].set(c[k]);
-            __syncthreads();
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int k = 0; k < 12; ++k) acc[k] = {0.f, 0.f};
-            LdsColumn ls{s};
-            GlobalLinks<P_F32, false> lk{links};
-            hopping_sum<float>(g, p, l, ls, lk, acc);
-            float cl[72];
-            CloverIO<float>::template load<false>(clover, blk, l, cl);
-            clover_apply(cl, c, y0);
+        for (int j = 0; j < 2; ++j) t.re[i][j] = t.im[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// acc += conj(q_row) y_col over four sites and the twelve components.  The
+// products of a step are summed on their own and then added: one chain of
+// products through all 16 steps of a wave would round each of its 768 terms
+// against the whole sum (2.2e-7 relative to 64 bits, 0.8e-7 before; now 0.6e-7).
+__device__ __forceinline__ void asm_products(const cpx<float>* q, const cpx<float>* y0, const cpx<float>* y1,
+                                             AsmTile& acc) {
+    AsmTile t;
+    asm_clear(t);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) y0[k] = {y0[k].re - kappa * acc[k].re, y0[k].im - kappa * acc[k].im};
+    for (int c = 0; c < 12; ++c) {
+        const int r = c / 6;
+        const float ar = q[c].re, ai = q[c].im;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const cpx<float> y = j ? y1[c] : y0[c];
+            t.re[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, y.re, t.re[r][j], 0, 0, 0);
+            t.im[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, y.im, t.im[r][j], 0, 0, 0);
         }
-        back_face<0>(g, p, l, links, P, fs, nv, col, kappa, yf[0]);
-        back_face<1>(g, p, l, links, P, fs, nv, col, kappa, yf[1]);
-        back_face<2>(g, p, l, links, P, fs, nv, col, kappa, yf[2]);
-        back_face<3>(g, p, l, links, P, fs, nv, col, kappa, yf[3]);
-        for (int i0 = 0; i0 < nv; i0 += ASM_R) {
-            // partial sums of this lane: value 20 r + 4 e + 2 chi + (re, im),
-            // e = 0 the self term, e = 1 + mu the -mu face
 #pragma unroll
-            for (int r = 0; r < ASM_R; ++r) {
-                float v[20];
-                if (i0 + r < nv) {
-                    cpx<float> q[12];
-                    load_f32(P, fs, i0 + r, g.nblk, blk, l, q);
-                    chi_dots(q, y0, v);
-#pragma unroll
-                    for (int mu = 0; mu < 4; ++mu) chi_dots(q, yf[mu], v + 4 + 4 * mu);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 20; ++k) v[k] = 0.f;
-                }
-#pragma unroll
-                for (int k = 0; k < 20; ++k) red[l * ASM_LD + 20 * r + k] = v[k];
-            }
-            __syncthreads();
-            // four partial sums of 64 lanes per value, then their fixed-order total
-            for (int w = l; w < 4 * ASM_VALS; w += TPB) {
-                const int val = w >> 2, seg = w & 3;
-                float sum = 0.f;
-                for (int j = 0; j < 64; ++j) sum += red[(seg * 64 + j) * ASM_LD + val];
-                part[val][seg] = sum;
-            }
-            __syncthreads();
-            for (int val = l; val < ASM_VALS; val += TPB) {
-                const int r = val / 20, rem = val % 20, e = rem >> 2, chi = (rem >> 1) & 1;
-                if ((rem & 1) == 0 && i0 + r < nv) {
-                    const float re = (part[val][0] + part[val][1]) + (part[val][2] + part[val][3]);
-                    const float im = (part[val + 1][0] + part[val + 1][1]) + (part[val + 1][2] + part[val + 1][3]);
-                    const int row = chi * nv + i0 + r, d = e == 0 ? 0 : 2 * e;  // e = 1 + mu -> d = 2 + 2 mu
-                    Dc[(((size_t)blk * 9 + d) * nc + col) * nc + row] = make_float2(re, im);
-                }
-            }
-            __syncthreads();  // red and part are reused by the next round
+        for (int j = 0; j < 2; ++j) {
+            const cpx<float> y = j ? y1[c] : y0[c];
+            t.re[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, y.im, t.re[r][j], 0, 0, 0);
+            t.im[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai, y.re, t.im[r][j], 0, 0, 0);
         }
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            acc.re[i][j] += t.re[i][j];
+            acc.im[i][j] += t.im[i][j];
+        }
+}
+
+template <int RT>
+__global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, const void* links, const void* clover,
+                                                                      float kappa, const char* P, size_t fs, int nv,
+                                                                      float2* Dc) {
+    const int nc = 2 * nv, w = xcd_remap(blockIdx.x, g.nblk * RT), blk = w / RT, ct = w % RT;
+    const BlockPos p = block_pos(g, blk);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, kk = lane >> 4;
+    const int col = 16 * ct + j;
+    const char* Pj = P + (size_t)(col < nv ? col : nv - 1) * fs;
+    const char* Pi[RT];  // the rows this lane supplies
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) Pi[rt] = P + (size_t)(16 * rt + j < nv ? 16 * rt + j : nv - 1) * fs;
+    AsmTile acc[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) asm_clear(acc[rt]);
+    // rows of this lane's sums: 4 kk + r of every row tile
+    auto store = [&](int d, int rt, int ri, int ci, int r, float re, float im) {
+        const int row = 16 * rt + 4 * kk + r;
+        if (col < nv && row < nv)
+            Dc[(((size_t)blk * 9 + d) * nc + ci * nv + col) * nc + ri * nv + row] = make_float2(re, im);
+    };
+
+    // ---- self term: wave = t slice, the four sites of a step one x row
+#pragma unroll 1
+    for (int s = 0; s < 16; ++s) {
+        const int l = kk + 4 * s + 64 * wave;
+        cpx<float> q[12], y0[12], y1[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) y0[k] = y1[k] = {0.f, 0.f};
+        hops_inside<0>(blk, l, links, Pj, g.nblk, y0, y1);
+        hops_inside<1>(blk, l, links, Pj, g.nblk, y0, y1);
+        hops_inside<2>(blk, l, links, Pj, g.nblk, y0, y1);
+        hops_inside<3>(blk, l, links, Pj, g.nblk, y0, y1);
+        SpinorIO<P_F32>::load(Pj, g.nblk, blk, l, q);
+        cpx<float> cq[12];
+        {
+            float cl[72];
+            CloverIO<float>::template load<false>(clover, blk, l, cl);
+            clover_apply(cl, q, cq);
+        }
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const cpx<float> c0 = k < 6 ? cq[k] : cpx<float>{0.f, 0.f}, c1 = k < 6 ? cpx<float>{0.f, 0.f} : cq[k];
+            y0[k] = {fmaf(-kappa, y0[k].re, c0.re), fmaf(-kappa, y0[k].im, c0.im)};
+            y1[k] = {fmaf(-kappa, y1[k].re, c1.re), fmaf(-kappa, y1[k].im, c1.im)};
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if (RT > 1) SpinorIO<P_F32>::load(Pi[rt], g.nblk, blk, l, q);
+            asm_products(q, y0, y1, acc[rt]);
+        }
+    }
+    // the four waves' sums in LDS, added in order by the wave of each
+    // (row, column) chirality pair
+    __shared__ float2 red[4][4][4][64];  // [wave][chirality pair][r][lane]
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        __syncthreads();  // the previous tile's readers are done
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                red[wave][q][r][lane] = make_float2(acc[rt].re[q >> 1][q & 1][r], acc[rt].im[q >> 1][q & 1][r]);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float2 a = red[0][wave][r][lane], b = red[1][wave][r][lane], c = red[2][wave][r][lane],
+                         d = red[3][wave][r][lane];
+            store(0, rt, wave >> 1, wave & 1, r, (a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y));
+        }
+        asm_clear(acc[rt]);
+    }
+
+    // ---- faces: wave mu takes the 64 sites of the -mu face, four to a step
+    // (an x row, or a y row of the x face)
+    const int mu = wave;
+#pragma unroll 1
+    for (int s = 0; s < 16; ++s) {
+        const int lo = s & 3, hi = s >> 2;
+        const int l = mu == 0 ? 4 * kk + 16 * lo + 64 * hi : mu == 1 ? kk + 16 * lo + 64 * hi
+                      : mu == 2 ? kk + 4 * lo + 64 * hi : kk + 4 * lo + 16 * hi;
+        cpx<float> y0[12], y1[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) y0[k] = y1[k] = {0.f, 0.f};
+        switch (mu) {
+        case 0: hop_back_face<0>(g, p, l, links, Pj, y0, y1); break;
+        case 1: hop_back_face<1>(g, p, l, links, Pj, y0, y1); break;
+        case 2: hop_back_face<2>(g, p, l, links, Pj, y0, y1); break;
+        default: hop_back_face<3>(g, p, l, links, Pj, y0, y1); break;
+        }
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            y0[k] = {-kappa * y0[k].re, -kappa * y0[k].im};
+            y1[k] = {-kappa * y1[k].re, -kappa * y1[k].im};
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            cpx<float> q[12];
+            SpinorIO<P_F32>::load(Pi[rt], g.nblk, blk, l, q);
+            asm_products(q, y0, y1, acc[rt]);
+        }
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                store(2 + 2 * mu, rt, q >> 1, q & 1, r, acc[rt].re[q >> 1][q & 1][r], acc[rt].im[q >> 1][q & 1][r]);
 }
 
 // D_c[a][1 + 2 mu] from gamma5-hermiticity of D (P keeps chirality):
@@ -1023,8 +1120,14 @@ hipError_t mg_orthonormalize(const Geom& g, void* P, int nv, hipStream_t s) {
 
 hipError_t mg_assemble(const OpData& op, const void* P, int nv, float2* Dc, hipStream_t s) {
     ProfScope ps("mg", s);
-    hipLaunchKernelGGL(k_mg_assemble, dim3(op.g.nblk * 2 * nv), dim3(TPB), 0, s, op.g, op.links[P_F32], op.clover32,
-                       (float)op.kappa, (const char*)P, spinor_bytes_per_site(P_F32) * op.g.V, nv, Dc);
+    static_assert(MG_MAX_NV <= 32, "two row tiles of 16");
+    const size_t fs = spinor_bytes_per_site(P_F32) * op.g.V;
+    if (nv <= 16)
+        hipLaunchKernelGGL(k_mg_assemble<1>, dim3(op.g.nblk), dim3(TPB), 0, s, op.g, op.links[P_F32], op.clover32,
+                           (float)op.kappa, (const char*)P, fs, nv, Dc);
+    else
+        hipLaunchKernelGGL(k_mg_assemble<2>, dim3(2 * op.g.nblk), dim3(TPB), 0, s, op.g, op.links[P_F32],
+                           op.clover32, (float)op.kappa, (const char*)P, fs, nv, Dc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mg_assemble_fwd, dim3(op.g.nblk, 4), dim3(TPB), 0, s, op.g, nv, Dc);
