@@ -112,8 +112,8 @@ __global__ __launch_bounds__(TPB) void k_mg_orthonormalize(Geom g, char* P, size
 // the operands of the products, the vector itself as row j of P^dag and D p as
 // column j, for four sites and one component at a time; nothing is transposed
 // or reduced across lanes.  Workgroup = (aggregate, 16 columns j of either
-// chirality): first the self term, one t slice per wave, summed over the waves
-// in LDS; then the faces, wave mu the -mu face.  RT row tiles of 16 cover nv
+// chirality): first the self term, a quarter of the sites per wave, summed over
+// the waves in LDS; then the faces, wave mu the -mu face.  RT row tiles of 16 cover nv
 // (rows and columns past nv repeat field nv - 1 and are not stored).
 // Per site and column about 1400 VALU instructions apply D and 96 products of
 // 32 cycles contract; with one column per workgroup and dot products reduced
@@ -251,10 +251,11 @@ __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, co
             Dc[(((size_t)blk * 9 + d) * nc + ci * nv + col) * nc + ri * nv + row] = make_float2(re, im);
     };
 
-    // ---- self term: wave = t slice, the four sites of a step one x row
+    // ---- self term: a step is an xy plane of the aggregate, a wave one of its
+    // x rows, so that the waves' neighbours meet in the L1
 #pragma unroll 1
     for (int s = 0; s < 16; ++s) {
-        const int l = kk + 4 * s + 64 * wave;
+        const int l = kk + 4 * wave + 16 * s;
         cpx<float> q[12], y0[12], y1[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) y0[k] = y1[k] = {0.f, 0.f};
