@@ -61,41 +61,124 @@ __device__ __forceinline__ int block_step(const Geom& g, const BlockPos& p, int 
 // ---------------------------------------------------------------- setup
 
 // Modified Gram-Schmidt of the nv fields per aggregate and chirality, in place.
+// One workgroup per (aggregate, chirality), lane = site, ORTHO_V vectors in
+// registers at a time: as soon as vector i is done, its dot products with all
+// later vectors of the group are summed together (one barrier per vector) and
+// it is projected out of them, so every v_j loses its components along q_0,
+// q_1, ... in that order and each field is read and written once per group of
+// ORTHO_V and read once more by every later group.  Bound by HBM: 32^3 x 64
+// with 16 vectors moves 6.4 GB; reading every earlier vector again for each
+// one, with a reduction per pair, took 4.7 ms.
+constexpr int ORTHO_V = 16;
+
+// n sums of re and im over the workgroup: partial sums of the waves in red
+// (one buffer per call parity, so one barrier is enough); total(k) adds them in
+// a fixed order.
+struct OrthoSums {
+    float4 (*red)[2 * ORTHO_V + 1];  // [2][value], one float per wave
+    int buf = 0;
+    __device__ __forceinline__ void put(int k, float v) {
+        v = wave_sum(v);
+        if ((threadIdx.x & 63) == 0) ((float*)&red[buf][k])[threadIdx.x >> 6] = v;
+    }
+    __device__ __forceinline__ float total(int k) const {
+        const float4 t = red[buf][k];
+        return (t.x + t.y) + (t.z + t.w);
+    }
+    __device__ __forceinline__ double total64(int k) const {
+        const float4 t = red[buf][k];
+        return ((double)t.x + t.y) + ((double)t.z + t.w);
+    }
+};
+
+__device__ __forceinline__ void ortho_dot(const cpx<float>* q, const cpx<float>* v, float& re, float& im) {
+    re = im = 0.f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        re += q[k].re * v[k].re + q[k].im * v[k].im;
+        im += q[k].re * v[k].im - q[k].im * v[k].re;
+    }
+}
+
 __global__ __launch_bounds__(TPB) void k_mg_orthonormalize(Geom g, char* P, size_t fs, int nv) {
-    const int blk = blockIdx.x, l = threadIdx.x;
-    __shared__ float red[4][4];
-    __shared__ float tot[4];
-    for (int i = 0; i < nv; ++i) {
-        cpx<float> v[12];
-        load_f32(P, fs, i, g.nblk, blk, l, v);
-        for (int j = 0; j < i; ++j) {
-            cpx<float> q[12];
-            load_f32(P, fs, j, g.nblk, blk, l, q);
-            float d[4] = {0.f, 0.f, 0.f, 0.f};  // <q, v> per chirality (re, im)
+    const int blk = blockIdx.x, chi = blockIdx.y, l = threadIdx.x;
+    __shared__ float4 red[2][2 * ORTHO_V + 1];
+    OrthoSums sums{red};
+    auto row = [&](int i) { return (float4*)(P + (size_t)i * fs) + ((size_t)blk * 6 + 3 * chi) * BLOCK_SITES + l; };
+    auto load = [&](int i, cpx<float>* v) {
+        const float4* p = row(i);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                const int o = k < 6 ? 0 : 2;
-                d[o] += q[k].re * v[k].re + q[k].im * v[k].im;
-                d[o + 1] += q[k].re * v[k].im - q[k].im * v[k].re;
-            }
-            block_sum<4>(d, red, tot);
+        for (int k = 0; k < 3; ++k) {
+            const float4 t = p[k * BLOCK_SITES];
+            v[2 * k] = {t.x, t.y};
+            v[2 * k + 1] = {t.z, t.w};
+        }
+    };
+    for (int j0 = 0; j0 < nv; j0 += ORTHO_V) {
+        const int n = nv - j0 < ORTHO_V ? nv - j0 : ORTHO_V;
+        cpx<float> v[ORTHO_V][6];
 #pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                const int o = k < 6 ? 0 : 2;
-                const cpx<float> c = {tot[o], tot[o + 1]};
-                v[k] = v[k] - c * q[k];
+        for (int j = 0; j < ORTHO_V; ++j)
+            if (j < n) load(j0 + j, v[j]);
+        // against the finished vectors of earlier groups
+#pragma unroll 1
+        for (int i = 0; i < j0; ++i) {
+            cpx<float> q[6];
+            load(i, q);
+#pragma unroll
+            for (int j = 0; j < ORTHO_V; ++j)
+                if (j < n) {
+                    float re, im;
+                    ortho_dot(q, v[j], re, im);
+                    sums.put(2 * j, re);
+                    sums.put(2 * j + 1, im);
+                }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < ORTHO_V; ++j)
+                if (j < n) {
+                    const cpx<float> c = {sums.total(2 * j), sums.total(2 * j + 1)};
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) v[j][k] = v[j][k] - c * q[k];
+                }
+            sums.buf ^= 1;
+        }
+        // within the group; the dots are taken with v_i before its norm is known
+#pragma unroll
+        for (int i = 0; i < ORTHO_V; ++i) {
+            if (i < n) {
+                float nn = 0.f;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) nn += v[i][k].re * v[i][k].re + v[i][k].im * v[i][k].im;
+                sums.put(2 * ORTHO_V, nn);
+#pragma unroll
+                for (int j = i + 1; j < ORTHO_V; ++j)
+                    if (j < n) {
+                        float re, im;
+                        ortho_dot(v[i], v[j], re, im);
+                        sums.put(2 * j, re);
+                        sums.put(2 * j + 1, im);
+                    }
+                __syncthreads();
+                const double t = sums.total64(2 * ORTHO_V);
+                const float s = t > 0. ? (float)(1. / sqrt(t)) : 0.f;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) v[i][k] = s * v[i][k];
+#pragma unroll
+                for (int j = i + 1; j < ORTHO_V; ++j)
+                    if (j < n) {
+                        const cpx<float> c = {s * sums.total(2 * j), s * sums.total(2 * j + 1)};
+#pragma unroll
+                        for (int k = 0; k < 6; ++k) v[j][k] = v[j][k] - c * v[i][k];
+                    }
+                sums.buf ^= 1;
+                float4* p = row(j0 + i);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    p[k * BLOCK_SITES] = make_float4(v[i][2 * k].re, v[i][2 * k].im, v[i][2 * k + 1].re, v[i][2 * k + 1].im);
             }
         }
-        float n[2] = {0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < 12; ++k) n[k < 6 ? 0 : 1] += v[k].re * v[k].re + v[k].im * v[k].im;
-        float nn[4] = {n[0], n[1], 0.f, 0.f};
-        block_sum<4>(nn, red, tot);
-        const float s0 = tot[0] > 0.f ? 1.f / sqrtf(tot[0]) : 0.f, s1 = tot[1] > 0.f ? 1.f / sqrtf(tot[1]) : 0.f;
-#pragma unroll
-        for (int k = 0; k < 12; ++k) v[k] = (k < 6 ? s0 : s1) * v[k];
-        SpinorIO<P_F32>::store(P + (size_t)i * fs, g.nblk, blk, l, v);
-        __syncthreads();  // the next i reads the stored field
+        // a lane reads back only what it stored itself
     }
 }
 
@@ -1114,7 +1197,7 @@ void with_nc(int nc, bool half, F&& f) {
 
 hipError_t mg_orthonormalize(const Geom& g, void* P, int nv, hipStream_t s) {
     ProfScope ps("mg", s);
-    hipLaunchKernelGGL(k_mg_orthonormalize, dim3(g.nblk), dim3(TPB), 0, s, g, (char*)P,
+    hipLaunchKernelGGL(k_mg_orthonormalize, dim3(g.nblk, 2), dim3(TPB), 0, s, g, (char*)P,
                        spinor_bytes_per_site(P_F32) * g.V, nv);
     return hipGetLastError();
 }
