@@ -475,6 +475,21 @@ __global__ __launch_bounds__(TPB) void k_mg_restrict(Geom g, const char* P, size
     }
 }
 
+// Workgroup -> (aggregate, part of the fields) for the transfers of many fields.
+// All parts of an aggregate read the same rows of P: they are consecutive
+// workgroups of one XCD (workgroup b runs on XCD b % 8), so that its L2 serves
+// all parts but the first.  32^3 x 64, 16 vectors, 4 parts: with the parts in
+// grid y every part read P from HBM.
+struct MgManyPlace {
+    int blk, part;
+};
+__device__ __forceinline__ MgManyPlace mg_many_place(int nblk, int parts, int b) {
+    const int whole = nblk / 8 * 8 * parts;
+    if (b >= whole) return {(nblk / 8 * 8) + (b - whole) / parts, (b - whole) % parts};
+    const int k = b / 8;
+    return {k / parts * 8 + b % 8, k % parts};
+}
+
 // The restriction of nr FP32 fields r_j (stride rs) into nr coarse vectors
 // (stride rcs), R fields per workgroup: each P row read serves all R, and
 // every r_j gets the sums of k_mg_restrict (same terms, same order).
@@ -482,7 +497,8 @@ template <int PP, int R>
 __global__ __launch_bounds__(TPB) void k_mg_restrict_many(Geom g, const char* P, size_t fs, int nv,
                                                           const char* rbase, size_t rs, int nr, float2* rcbase,
                                                           size_t rcs) {
-    const int blk = blockIdx.x, l = threadIdx.x, j0 = blockIdx.y * R;
+    const auto [blk, part] = mg_many_place(g.nblk, (nr + R - 1) / R, blockIdx.x);
+    const int l = threadIdx.x, j0 = part * R;
     __shared__ float red[4][8 * R];
     __shared__ float tot[8 * R];
     cpx<float> rv[R][12];
@@ -545,7 +561,8 @@ template <int PP, int R>
 __global__ __launch_bounds__(TPB) void k_mg_prolong_many(Geom g, const char* P, size_t fs, int nv,
                                                          const float2* ecbase, size_t ecs, int nr, char* zbase,
                                                          size_t zs) {
-    const int blk = blockIdx.x, l = threadIdx.x, j0 = blockIdx.y * R;
+    const auto [blk, part] = mg_many_place(g.nblk, (nr + R - 1) / R, blockIdx.x);
+    const int l = threadIdx.x, j0 = part * R;
     cpx<float> o[R][12];
 #pragma unroll
     for (int j = 0; j < R; ++j)
@@ -1244,7 +1261,7 @@ hipError_t mg_restrict_many(const Geom& g, Transfer T, int nv, const void* r, in
     constexpr int R = 4;
     const size_t fs = spinor_bytes_per_site(T.prec) * g.V, rs = spinor_bytes_per_site(P_F32) * g.V;
     const size_t rcs = (size_t)g.nblk * 2 * nv;
-    const dim3 grid(g.nblk, (nr + R - 1) / R);
+    const dim3 grid(g.nblk * ((nr + R - 1) / R));
     if (T.prec == P_F16)
         hipLaunchKernelGGL((k_mg_restrict_many<P_F16, R>), grid, dim3(TPB), 0, s, g, (const char*)T.P, fs, nv,
                            (const char*)r, rs, nr, rc, rcs);
@@ -1259,7 +1276,7 @@ hipError_t mg_prolong_many(const Geom& g, Transfer T, int nv, const float2* ec, 
     ProfScope ps("mg", s);
     constexpr int R = 4;
     const size_t fs = spinor_bytes_per_site(T.prec) * g.V, zs = spinor_bytes_per_site(P_F32) * g.V;
-    const dim3 grid(g.nblk, (nr + R - 1) / R);
+    const dim3 grid(g.nblk * ((nr + R - 1) / R));
     if (T.prec == P_F16)
         hipLaunchKernelGGL((k_mg_prolong_many<P_F16, R>), grid, dim3(TPB), 0, s, g, (const char*)T.P, fs, nv, ec,
                            ecs, nr, (char*)z, zs);
