@@ -11,6 +11,7 @@
 // its -mu neighbour (entries that reach the same aggregate through different
 // faces stay separate, so the stencil is exact on any lattice).
 #include <type_traits>
+#include <utility>
 
 #include "blas.hpp"
 #include "dslash_core.hpp"
@@ -23,16 +24,19 @@ namespace {
 
 constexpr int TPB = BLOCK_SITES;
 
-// Sum N values over the workgroup; afterwards out[k] (LDS) holds total k.
+// Sum N values over the workgroup; afterwards out[k] (LDS) holds total k.  The
+// folded wave sums carry the restriction of many fields: with one sum per value
+// 32^3 x 64, 16 vectors took 2.30 ms, with these 1.61 ms.
 template <int N>
 __device__ __forceinline__ void block_sum(const float* v, float (*red)[N], float* out) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float t[N];
 #pragma unroll
-    for (int k = 0; k < N; ++k) t[k] = wave_sum(v[k]);
-    if (lane == 0) {
+    for (int k = 0; k < N; ++k) t[k] = v[k];
+    wave_sums<N>(t);
+    if (lane % 16 == 0) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) red[wave][k] = t[k];
+        for (int k = 0; k < N / 4; ++k) red[wave][k + lane / 16 * (N / 4)] = t[k];
     }
     __syncthreads();
     if ((int)threadIdx.x < N) {
@@ -65,31 +69,14 @@ __device__ __forceinline__ int block_step(const Geom& g, const BlockPos& p, int 
 // registers at a time: as soon as vector i is done, its dot products with all
 // later vectors of the group are summed together (one barrier per vector) and
 // it is projected out of them, so every v_j loses its components along q_0,
-// q_1, ... in that order and each field is read and written once per group of
-// ORTHO_V and read once more by every later group.  Bound by HBM: 32^3 x 64
-// with 16 vectors moves 6.4 GB; reading every earlier vector again for each
-// one, with a reduction per pair, took 4.7 ms.
-constexpr int ORTHO_V = 16;
-
-// n sums of re and im over the workgroup: partial sums of the waves in red
-// (one buffer per call parity, so one barrier is enough); total(k) adds them in
-// a fixed order.
-struct OrthoSums {
-    float4 (*red)[2 * ORTHO_V + 1];  // [2][value], one float per wave
-    int buf = 0;
-    __device__ __forceinline__ void put(int k, float v) {
-        v = wave_sum(v);
-        if ((threadIdx.x & 63) == 0) ((float*)&red[buf][k])[threadIdx.x >> 6] = v;
-    }
-    __device__ __forceinline__ float total(int k) const {
-        const float4 t = red[buf][k];
-        return (t.x + t.y) + (t.z + t.w);
-    }
-    __device__ __forceinline__ double total64(int k) const {
-        const float4 t = red[buf][k];
-        return ((double)t.x + t.y) + ((double)t.z + t.w);
-    }
-};
+// q_1, ... in that order and each field is read and written once, and read once
+// more by every later group.  The dots are taken with v_i before its norm is
+// known; the norm is inverted in 64 bits.  Groups of 8 leave room for three
+// workgroups per CU, which cover one another's chain of sums: 32^3 x 64 with 16
+// vectors takes 1.42 ms for 8 GB (16 vectors at a time, two workgroups per CU:
+// 1.47 ms for 6.4 GB).  Reading every earlier vector again for each one, with a
+// reduction per pair, took 4.4 ms.
+constexpr int ORTHO_V = 8;
 
 __device__ __forceinline__ void ortho_dot(const cpx<float>* q, const cpx<float>* v, float& re, float& im) {
     re = im = 0.f;
@@ -100,85 +87,119 @@ __device__ __forceinline__ void ortho_dot(const cpx<float>* q, const cpx<float>*
     }
 }
 
+// Sums over the workgroup: the waves' parts of N values into red (one float4
+// per value), in order of the value; the total of value k is the sum of red[k].
+template <int N>
+__device__ __forceinline__ void ortho_put(float* t, float4* red) {
+    wave_sums<N>(t);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane % 16 == 0) {
+#pragma unroll
+        for (int k = 0; k < N / 4; ++k) ((float*)&red[k + lane / 16 * (N / 4)])[wave] = t[k];
+    }
+}
+
+// The dots of q with v_J, v_{J + 1}, ... into red[2 J], ...
+template <int J>
+__device__ __forceinline__ void ortho_dots(const cpx<float>* q, const cpx<float> (*v)[6], float4* red) {
+    constexpr int W = (ORTHO_V - J + 1) / 2 * 2;  // a multiple of 4 sums
+    float t[2 * W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        t[2 * j] = t[2 * j + 1] = 0.f;
+        if (J + j < ORTHO_V) ortho_dot(q, v[J + j < ORTHO_V ? J + j : 0], t[2 * j], t[2 * j + 1]);
+        __builtin_amdgcn_sched_barrier(0);  // one dot at a time: interleaved, they need more registers
+    }
+    ortho_put<2 * W>(t, red + 2 * J);
+}
+__device__ __forceinline__ float ortho_total(const float4* red, int k) {
+    const float4 t = red[k];
+    return (t.x + t.y) + (t.z + t.w);
+}
+
+// One step within a group: vector I is finished and projected out of the later ones.
+template <int I>
+__device__ __forceinline__ void ortho_step(cpx<float> (*v)[6], float4 (*red)[2 * ORTHO_V + 2], int& buf) {
+    float4* r = red[buf];
+    float nn32 = 0.f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) nn32 += v[I][k].re * v[I][k].re + v[I][k].im * v[I][k].im;
+    nn32 = wave_sum(nn32);
+    if ((threadIdx.x & 63) == 0) ((float*)&r[2 * I])[threadIdx.x >> 6] = nn32;
+    if constexpr (I + 1 < ORTHO_V) ortho_dots<I + 1>(v[I], v, r);
+    __syncthreads();
+    const float4 n4 = r[2 * I];
+    const double nn = ((double)n4.x + n4.y) + ((double)n4.z + n4.w);
+    const float s = nn > 0. ? (float)(1. / sqrt(nn)) : 0.f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[I][k] = s * v[I][k];
+#pragma unroll
+    for (int j = I + 1; j < ORTHO_V; ++j) {
+        const cpx<float> c = {s * ortho_total(r, 2 * j), s * ortho_total(r, 2 * j + 1)};
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[j][k] = v[j][k] - c * v[I][k];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    buf ^= 1;
+}
+template <int... I>
+__device__ __forceinline__ void ortho_steps(cpx<float> (*v)[6], float4 (*red)[2 * ORTHO_V + 2], int n, int& buf,
+                                            std::integer_sequence<int, I...>) {
+    ((I < n ? ortho_step<I>(v, red, buf) : (void)0), ...);
+}
+
 __global__ __launch_bounds__(TPB) void k_mg_orthonormalize(Geom g, char* P, size_t fs, int nv) {
     const int blk = blockIdx.x, chi = blockIdx.y, l = threadIdx.x;
-    __shared__ float4 red[2][2 * ORTHO_V + 1];
-    OrthoSums sums{red};
-    auto row = [&](int i) { return (float4*)(P + (size_t)i * fs) + ((size_t)blk * 6 + 3 * chi) * BLOCK_SITES + l; };
+    __shared__ float4 red[2][2 * ORTHO_V + 2];
+    int buf = 0;  // two buffers, so that one barrier per sum is enough
+    // uniform row address + lane offset, so that no per-lane pointers are held
+    auto row = [&](int i, int k) {
+        return P + (size_t)i * fs + ((size_t)blk * 6 + 3 * chi + k) * (BLOCK_SITES * sizeof(float4));
+    };
+    const unsigned lane_off = l * sizeof(float4);
     auto load = [&](int i, cpx<float>* v) {
-        const float4* p = row(i);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const float4 t = p[k * BLOCK_SITES];
+            const float4 t = *(const float4*)(row(i, k) + lane_off);
             v[2 * k] = {t.x, t.y};
             v[2 * k + 1] = {t.z, t.w};
         }
     };
+#pragma unroll 1
     for (int j0 = 0; j0 < nv; j0 += ORTHO_V) {
         const int n = nv - j0 < ORTHO_V ? nv - j0 : ORTHO_V;
         cpx<float> v[ORTHO_V][6];
 #pragma unroll
-        for (int j = 0; j < ORTHO_V; ++j)
+        for (int j = 0; j < ORTHO_V; ++j) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[j][k] = {0.f, 0.f};  // past the last vector
             if (j < n) load(j0 + j, v[j]);
-        // against the finished vectors of earlier groups
+        }
+        // against the finished vectors of earlier groups, read back by the lane that stored them
 #pragma unroll 1
         for (int i = 0; i < j0; ++i) {
             cpx<float> q[6];
             load(i, q);
-#pragma unroll
-            for (int j = 0; j < ORTHO_V; ++j)
-                if (j < n) {
-                    float re, im;
-                    ortho_dot(q, v[j], re, im);
-                    sums.put(2 * j, re);
-                    sums.put(2 * j + 1, im);
-                }
+            ortho_dots<0>(q, v, red[buf]);
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < ORTHO_V; ++j)
-                if (j < n) {
-                    const cpx<float> c = {sums.total(2 * j), sums.total(2 * j + 1)};
+            for (int j = 0; j < ORTHO_V; ++j) {
+                const cpx<float> c = {ortho_total(red[buf], 2 * j), ortho_total(red[buf], 2 * j + 1)};
 #pragma unroll
-                    for (int k = 0; k < 6; ++k) v[j][k] = v[j][k] - c * q[k];
-                }
-            sums.buf ^= 1;
+                for (int k = 0; k < 6; ++k) v[j][k] = v[j][k] - c * q[k];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            buf ^= 1;
         }
-        // within the group; the dots are taken with v_i before its norm is known
+        ortho_steps(v, red, n, buf, std::make_integer_sequence<int, ORTHO_V>{});
 #pragma unroll
-        for (int i = 0; i < ORTHO_V; ++i) {
-            if (i < n) {
-                float nn = 0.f;
-#pragma unroll
-                for (int k = 0; k < 6; ++k) nn += v[i][k].re * v[i][k].re + v[i][k].im * v[i][k].im;
-                sums.put(2 * ORTHO_V, nn);
-#pragma unroll
-                for (int j = i + 1; j < ORTHO_V; ++j)
-                    if (j < n) {
-                        float re, im;
-                        ortho_dot(v[i], v[j], re, im);
-                        sums.put(2 * j, re);
-                        sums.put(2 * j + 1, im);
-                    }
-                __syncthreads();
-                const double t = sums.total64(2 * ORTHO_V);
-                const float s = t > 0. ? (float)(1. / sqrt(t)) : 0.f;
-#pragma unroll
-                for (int k = 0; k < 6; ++k) v[i][k] = s * v[i][k];
-#pragma unroll
-                for (int j = i + 1; j < ORTHO_V; ++j)
-                    if (j < n) {
-                        const cpx<float> c = {s * sums.total(2 * j), s * sums.total(2 * j + 1)};
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) v[j][k] = v[j][k] - c * v[i][k];
-                    }
-                sums.buf ^= 1;
-                float4* p = row(j0 + i);
+        for (int j = 0; j < ORTHO_V; ++j)
+            if (j < n) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
-                    p[k * BLOCK_SITES] = make_float4(v[i][2 * k].re, v[i][2 * k].im, v[i][2 * k + 1].re, v[i][2 * k + 1].im);
+                    *(float4*)(row(j0 + j, k) + lane_off) =
+                        make_float4(v[j][2 * k].re, v[j][2 * k].im, v[j][2 * k + 1].re, v[j][2 * k + 1].im);
             }
-        }
-        // a lane reads back only what it stored itself
     }
 }
 
@@ -479,7 +500,7 @@ __global__ __launch_bounds__(TPB) void k_mg_restrict(Geom g, const char* P, size
 // All parts of an aggregate read the same rows of P: they are consecutive
 // workgroups of one XCD (workgroup b runs on XCD b % 8), so that its L2 serves
 // all parts but the first.  32^3 x 64, 16 vectors, 4 parts: with the parts in
-// grid y every part read P from HBM.
+// grid y every part read P from HBM (prolong 3.03 ms, now 1.49 ms).
 struct MgManyPlace {
     int blk, part;
 };

@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace cs {
 
 namespace wave_detail {
@@ -76,6 +78,32 @@ __device__ __forceinline__ T wave_sum(T v) {
     v += dpp_move<DPP_MIRROR>(v);
     v = cross_add<16>(v);
     return cross_add<32>(v);
+}
+
+// Sums of N values (a multiple of 4) over the wave.  The values are folded
+// pairwise as the lanes are halved (one swap and one add serve two values),
+// then summed within rows of 16 lanes: 2.75 N instructions where a sum per
+// value takes 8 N.  Afterwards every lane of row r (lane / 16) holds the total
+// of value k + r * (N / 4) in v[k], k < N / 4.
+template <int N>
+__device__ __forceinline__ void wave_sums(float* v) {
+    using namespace wave_detail;
+    static_assert(N % 4 == 0);
+    auto fold = [](float a, float b, auto w) {
+        unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+        swap_u32<decltype(w)::value>(x, y);
+        return __uint_as_float(x) + __uint_as_float(y);
+    };
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) v[k] = fold(v[k], v[k + N / 2], std::integral_constant<int, 32>{});
+#pragma unroll
+    for (int k = 0; k < N / 4; ++k) {
+        float u = fold(v[k], v[k + N / 4], std::integral_constant<int, 16>{});
+        u += dpp_move<DPP_XOR1>(u);
+        u += dpp_move<DPP_XOR2>(u);
+        u += dpp_move<DPP_HALF_MIRROR>(u);
+        v[k] = u + dpp_move<DPP_MIRROR>(u);
+    }
 }
 
 // Lane pairs (i, i + 32), i < 32.  Both lanes of a pair receive from_lo = v
