@@ -37,16 +37,13 @@ constexpr int BLOCK_SITES = 256;  // one 4^4 block = one workgroup
 
 // Tuning knobs (compile-time; the defaults are the measured best on MI355X).
 // Minimum waves per SIMD requested from the register allocator for the
-// operator and smoother kernels (0 = compiler default); XCD-aware ordering of
+// operator kernels (0 = compiler default); XCD-aware ordering of
 // workgroups; non-temporal loads of the fields that are read exactly once
 // (links, clover) and non-temporal stores of FP32 spinor fields, which keeps
 // the caches for the face neighbours that are read twice; a raised wave
 // priority during the loads of a SAP block visit.
 #ifndef CS_DSLASH_WAVES
 #define CS_DSLASH_WAVES 0
-#endif
-#ifndef CS_SAP_WAVES
-#define CS_SAP_WAVES 0
 #endif
 #ifndef CS_XCD_REMAP
 #define CS_XCD_REMAP 1
@@ -70,11 +67,6 @@ constexpr int BLOCK_SITES = 256;  // one 4^4 block = one workgroup
 #define CS_DSLASH_BOUNDS __launch_bounds__(256, CS_DSLASH_WAVES)
 #else
 #define CS_DSLASH_BOUNDS __launch_bounds__(256)
-#endif
-#if CS_SAP_WAVES > 0
-#define CS_SAP_BOUNDS __launch_bounds__(256, CS_SAP_WAVES)
-#else
-#define CS_SAP_BOUNDS __launch_bounds__(256)
 #endif
 
 // MI355X dispatches consecutive workgroups round-robin over its 8 XCDs, each

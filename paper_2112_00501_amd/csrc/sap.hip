@@ -29,9 +29,15 @@ struct LinkSmem { lds_cpx<float> u[4][6][BLOCK_SITES]; };
 template <>
 struct LinkSmem<false> { lds_cpx<float> u[1][1][1]; };
 
+// Sites of a row of rho in LDS.  Behind the block's own sites the FP32 rows hold
+// 64 zeros: a lane whose neighbour lies outside the block reads one of them, so
+// that no hop branches.
+template <typename R>
+constexpr int RHO_ROW = std::is_same<R, float>::value ? BLOCK_SITES + 64 : BLOCK_SITES;
+
 template <typename R>
 struct LdsSpinor {  // in-block neighbours of the Dirichlet operator
-    lds_cpx<R> (*s)[BLOCK_SITES];
+    lds_cpx<R> (*s)[RHO_ROW<R>];
     __device__ __forceinline__ bool want(bool inside) const { return inside; }
     template <typename RR>
     __device__ __forceinline__ void load_nb(int, int l, bool, cpx<RR>* c) const {
@@ -47,41 +53,73 @@ struct OwnRow2 {
     cpx<float> r[4][3];
 };
 
-// acc += the two hops of direction MU that stay inside the block (Dirichlet
-// block operator), neighbours and links read from LDS; the same terms in the
-// same order as the general hopping sum
-template <int MU, typename R>
-__device__ __forceinline__ void block_hop_dir(int l, const LdsSpinor<R>& ls, const LinkSmem<true>& sm,
-                                              const OwnRow2& own, cpx<R>* acc) {
-    constexpr int sh = 2 * MU;
-    const int lc = (l >> sh) & 3;
-    if (lc < 3) {  // forward neighbour, own link U_mu(x)
-        cpx<R> psi[12], u[9];
-        ls.load_nb(0, l + (1 << sh), true, psi);
+// Keeps the loads that follow behind the values computed so far, and their
+// addresses with them: issued or computed earlier they would need more than
+// the 256 registers that leave room for two workgroups per CU.
+template <typename R>
+__device__ __forceinline__ void hold(cpx<R>* v, int& l) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) u[k] = {(R)sm.u[MU][k][l].re, (R)sm.u[MU][k][l].im};
-#pragma unroll
-        for (int k = 0; k < 3; ++k) u[6 + k] = {(R)own.r[MU][k].re, (R)own.r[MU][k].im};
-        hop_term<MU, -1>(u, psi, acc);
-    }
-    if (lc > 0) {  // backward neighbour, its link U_mu(x - mu)
-        const int nl = l - (1 << sh);
-        cpx<R> psi[12], u[9];
-        ls.load_nb(0, nl, true, psi);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) u[k] = {(R)sm.u[MU][k][nl].re, (R)sm.u[MU][k][nl].im};
-        su3_row2(u);
-        hop_term<MU, +1>(u, psi, acc);
-    }
+    for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(v[k].re), "+v"(v[k].im)::"memory");
+    asm volatile("" : "+v"(l));
 }
 
+// Operands of hop H inside the block (H = 2 mu forward, 2 mu + 1 backward) from
+// LDS: the neighbour's rho and rows 0 and 1 of U_mu(x), or of U_mu(x - mu).  A
+// lane whose neighbour lies outside the block reads the zero in the bank that
+// the neighbour one block further would have, which no other lane then uses.
+struct BlockHop {
+    cpx<float> psi[12], u[6];
+};
+template <int H>
+__device__ __forceinline__ void block_hop_fetch(int l, const LdsSpinor<float>& ls, const LinkSmem<true>& sm,
+                                                BlockHop& o) {
+    constexpr int MU = H / 2, sh = 2 * MU, back = H & 1;
+    const int lc = (l >> sh) & 3;
+    const bool in = back ? lc > 0 : lc < 3;
+    const int wrapped = (l & ~(3 << sh)) | (((lc + (back ? 3 : 1)) & 3) << sh);
+    const int nl = in ? wrapped : BLOCK_SITES + (wrapped & 63);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) o.psi[k] = ls.s[k][nl].get();
+    const int ul = back ? wrapped : l;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) o.u[k] = sm.u[MU][k][ul].get();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// acc += the hops that stay inside the block (Dirichlet block operator).  The
+// operands of the next hop are on their way from LDS while the current one is
+// computed: with a wave or two per SIMD nothing else hides that latency.  Four
+// MR steps of a block take 36.5 thousand cycles with two workgroups per CU and
+// 32.5 alone; fetching each hop when it was due, 39 and 36.6.
+template <int H = 0>
+__device__ __forceinline__ void block_hops_from(int l, const LdsSpinor<float>& ls, const LinkSmem<true>& sm,
+                                                const OwnRow2& own, const BlockHop& cur, cpx<float>* acc) {
+    constexpr int MU = H / 2;
+    BlockHop next;
+    if constexpr (H < 7) block_hop_fetch<H + 1>(l, ls, sm, next);
+    cpx<float> u[9];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) u[k] = cur.u[k];
+    if constexpr (H % 2 == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) u[6 + k] = own.r[MU][k];
+        hop_term<MU, -1>(u, cur.psi, acc);
+    } else {
+        su3_row2(u);
+        hop_term<MU, +1>(u, cur.psi, acc);
+    }
+    if constexpr (H < 7) {
+        __builtin_amdgcn_sched_barrier(0);
+        block_hops_from<H + 1>(l, ls, sm, own, next, acc);
+    }
+}
 template <typename R>
 __device__ __forceinline__ void block_hops(int l, const LdsSpinor<R>& ls, const LinkSmem<true>& sm,
                                            const OwnRow2& own, cpx<R>* acc) {
-    block_hop_dir<0>(l, ls, sm, own, acc);
-    block_hop_dir<1>(l, ls, sm, own, acc);
-    block_hop_dir<2>(l, ls, sm, own, acc);
-    block_hop_dir<3>(l, ls, sm, own, acc);
+    BlockHop first;
+    block_hop_fetch<0>(l, ls, sm, first);
+    block_hops_from<0>(l, ls, sm, own, first, acc);
 }
 
 // x is zero on the blocks of the current colour: only hops that leave the
@@ -320,7 +358,7 @@ __device__ __forceinline__ void block_sum3(R& a, R& b, R& c, R (*red)[4]) {
 // half-sweeps of a cycle that start from x = 0 (modes 1 and 2) share the
 // other instantiation.
 template <int P, int PLINK, int BS, bool GEN>
-__global__ CS_SAP_BOUNDS void k_sap_halfsweep(Geom g, const void* __restrict__ links,
+__global__ __launch_bounds__(256, P != P_F64 && BS != BLOCK_EO ? 2 : 1) void k_sap_halfsweep(Geom g, const void* __restrict__ links,
                                               const void* __restrict__ clover,
                                               const void* __restrict__ cinv, double kappa_d,
                                               int colour, int n_mr, int mode_in, void* __restrict__ x,
@@ -328,7 +366,7 @@ __global__ CS_SAP_BOUNDS void k_sap_halfsweep(Geom g, const void* __restrict__ l
                                               int tile, int nitems) {
     using R = typename Arith<P>::R;
     constexpr bool F32PATH = std::is_same<R, float>::value;
-    __shared__ lds_cpx<R> s_rho[12][BLOCK_SITES];
+    __shared__ lds_cpx<R> s_rho[12][RHO_ROW<R>];
     // FP64 Jacobi keeps the block residual in LDS instead of registers (the
     // FP64 kernel runs one workgroup per compute unit either way)
     constexpr bool RHO_LDS = BS == BLOCK_JACOBI && !F32PATH;
@@ -344,6 +382,9 @@ __global__ CS_SAP_BOUNDS void k_sap_halfsweep(Geom g, const void* __restrict__ l
     const R kappa = (R)kappa_d;
     const int mode = GEN ? 0 : mode_in;
     LdsSpinor<R> ls{s_rho};
+    if constexpr (F32PATH) {  // read after the first barrier below
+        for (int k = threadIdx.x; k < 12 * 64; k += BLOCK_SITES) s_rho[k / 64][BLOCK_SITES + k % 64] = {(R)0, (R)0};
+    }
 
     for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
         const int w = xcd_remap(item, nitems);
@@ -398,16 +439,22 @@ __global__ CS_SAP_BOUNDS void k_sap_halfsweep(Geom g, const void* __restrict__ l
                 if (mode == 0) {
                     using RS = typename SpinorIO<P>::R;
                     cpx<RS> t[12];
-                    SpinorIO<P>::load(xr, g.nblk, blk, l, t);
+                    int lx = l;
+                    asm volatile("" : "+v"(lx));
+                    SpinorIO<P>::load(xr, g.nblk, blk, lx, t);
                     __syncthreads();  // the previous right-hand side's readers of rho are done
 #pragma unroll
                     for (int k = 0; k < 12; ++k) s_rho[k][l] = {(R)t[k].re, (R)t[k].im};
                     __syncthreads();
                     block_hops<R>(l, ls, s_lk, own, acc);
                 }
+                int lf = l;
+                hold(acc, lf);
                 if (mode != 1) {
-                    face_pair<0, 1, P, R>(g, p, l, xr, links, acc);
-                    face_pair<2, 3, P, R>(g, p, l, xr, links, acc);
+                    face_pair<0, 1, P, R>(g, p, lf, xr, links, acc);
+                    hold(acc, lf);
+                    face_pair<2, 3, P, R>(g, p, lf, xr, links, acc);
+                    hold(acc, lf);
                 }
                 cpx<R> cx[12];
                 cpx<R> self[12];
@@ -420,7 +467,7 @@ __global__ CS_SAP_BOUNDS void k_sap_halfsweep(Geom g, const void* __restrict__ l
                 }
                 using RS = typename SpinorIO<P>::R;
                 cpx<RS> t[12];
-                SpinorIO<P>::load(br, g.nblk, blk, l, t);
+                SpinorIO<P>::load(br, g.nblk, blk, lf, t);
                 if constexpr (BS != BLOCK_JACOBI) {
 #pragma unroll
                     for (int k = 0; k < 12; ++k)
@@ -707,15 +754,17 @@ __global__ CS_SAP_BOUNDS void k_sap_halfsweep(Geom g, const void* __restrict__ l
             __syncthreads();
             using RS = typename SpinorIO<P>::R;
             cpx<RS> xo[12];
+            int lo = l;
+            asm volatile("" : "+v"(lo));
             if (mode == 0) {
-                SpinorIO<P>::load(xr, g.nblk, blk, l, xo);
+                SpinorIO<P>::load(xr, g.nblk, blk, lo, xo);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) xo[k] = {xo[k].re + (RS)delta[k].re, xo[k].im + (RS)delta[k].im};
             } else {
 #pragma unroll
                 for (int k = 0; k < 12; ++k) xo[k] = {(RS)delta[k].re, (RS)delta[k].im};
             }
-            SpinorIO<P>::store(xr, g.nblk, blk, l, xo);
+            SpinorIO<P>::store(xr, g.nblk, blk, lo, xo);
         }
     }
 }
