@@ -81,60 +81,67 @@ struct RawLink<P_F16> : RawLink16<P_F16> {};
 template <>
 struct RawLink<P_BF16> : RawLink16<P_BF16> {};
 
-template <int PIN, int PLINK>
+// One hop's operands for G right-hand sides, fields in_stride apart.
+template <int PIN, int PLINK, int G>
 struct RawHop {
-    RawSpinor<PIN> psi;
+    RawSpinor<PIN> psi[G];
     RawLink<PLINK> link;
     template <int H>
-    __device__ __forceinline__ void load(const Geom& g, const BlockPos& p, int l, const void* in, const void* links) {
+    __device__ __forceinline__ void load(const Geom& g, const BlockPos& p, int l, const void* in, size_t in_stride,
+                                         const void* links) {
         constexpr int MU = H >> 1, DIR = (H & 1) ? -1 : +1;
         int nl;
         bool inside;
         const int nb = neighbour(g, p, l, MU, DIR, &nl, &inside);
-        psi.load(in, g.nblk, nb, nl);
+#pragma unroll
+        for (int j = 0; j < G; ++j) psi[j].load((const char*)in + j * in_stride, g.nblk, nb, nl);
         link.load(links, DIR > 0 ? p.blk : nb, DIR > 0 ? l : nl, MU);
     }
     template <int H, bool DAG, typename R>
-    __device__ __forceinline__ void apply(const Geom& g, const BlockPos& p, int l, cpx<R>* acc) const {
+    __device__ __forceinline__ void apply(const Geom& g, const BlockPos& p, int l, cpx<R> (*acc)[12]) const {
         constexpr int MU = H >> 1, DIR = (H & 1) ? -1 : +1, lc = DIR > 0 ? 3 : 0;
-        cpx<R> c[12], u[9];
-        psi.get(c);
-        link.get(u);
-        if (DAG) negate_lower(c);
-        if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, DIR, ((l >> 6) & 3) != lc), &c[0].re, 24);
-        su3_row2(u);
-        hop_term<MU, -DIR>(u, c, acc);
+        cpx<R> u[9];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            cpx<R> c[12];
+            psi[j].get(c);
+            if (DAG) negate_lower(c);
+            if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, DIR, ((l >> 6) & 3) != lc), &c[0].re, 24);
+            if (j == 0) {
+                link.get(u);
+                su3_row2(u);
+            }
+            hop_term<MU, -DIR>(u, c, acc[j]);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(acc[j][k].re), "+v"(acc[j][k].im));
+        }
     }
 };
 
-template <int H, int AHEAD, bool DAG, typename HOP, typename R>
-__device__ __forceinline__ void hops_ahead(const Geom& g, const BlockPos& p, int l, const void* in,
-                                           const void* links, HOP* f, cpx<R>* acc) {
+template <int H, int AHEAD, bool DAG, int G, typename HOP, typename R>
+__device__ __forceinline__ void hops_ahead(const Geom& g, const BlockPos& p, int l, const void* in, size_t in_stride,
+                                           const void* links, HOP* f, cpx<R> (*acc)[12]) {
     if constexpr (H < 8) {
         constexpr int N = AHEAD + 1;
-        if constexpr (H + AHEAD < 8) f[(H + AHEAD) % N].template load<H + AHEAD>(g, p, l, in, links);
+        if constexpr (H + AHEAD < 8) f[(H + AHEAD) % N].template load<H + AHEAD>(g, p, l, in, in_stride, links);
         // the fetch stays before this hop's arithmetic and the arithmetic here,
         // or the compiler would issue all loads first and spill
         __builtin_amdgcn_sched_barrier(0);
         f[H % N].template apply<H, DAG>(g, p, l, acc);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(acc[k].re), "+v"(acc[k].im));
         __builtin_amdgcn_sched_barrier(0);
-        hops_ahead<H + 1, AHEAD, DAG>(g, p, l, in, links, f, acc);
+        hops_ahead<H + 1, AHEAD, DAG, G>(g, p, l, in, in_stride, links, f, acc);
     }
 }
 
-template <int PIN, int PLINK, int AHEAD, bool DAG, typename R>
+template <int PIN, int PLINK, int AHEAD, bool DAG, int G, typename R>
 __device__ __forceinline__ void hopping_sum_ahead(const Geom& g, const BlockPos& p, int l, const void* in,
-                                                  const void* links, cpx<R>* acc) {
-    static_assert(AHEAD >= 1 && AHEAD <= 5, "the first hops fetched here");
-    RawHop<PIN, PLINK> f[AHEAD + 1];
-    f[0].template load<0>(g, p, l, in, links);
-    if constexpr (AHEAD > 1) f[1].template load<1>(g, p, l, in, links);
-    if constexpr (AHEAD > 2) f[2].template load<2>(g, p, l, in, links);
-    if constexpr (AHEAD > 3) f[3].template load<3>(g, p, l, in, links);
-    if constexpr (AHEAD > 4) f[4].template load<4>(g, p, l, in, links);
-    hops_ahead<0, AHEAD, DAG>(g, p, l, in, links, f, acc);
+                                                  size_t in_stride, const void* links, cpx<R> (*acc)[12]) {
+    static_assert(AHEAD >= 1 && AHEAD <= 3, "the first hops fetched here");
+    RawHop<PIN, PLINK, G> f[AHEAD + 1];
+    f[0].template load<0>(g, p, l, in, in_stride, links);
+    if constexpr (AHEAD > 1) f[1].template load<1>(g, p, l, in, in_stride, links);
+    if constexpr (AHEAD > 2) f[2].template load<2>(g, p, l, in, in_stride, links);
+    hops_ahead<0, AHEAD, DAG, G>(g, p, l, in, in_stride, links, f, acc);
 }
 
 // One right-hand side per workgroup.  Bound by HBM on large lattices (per
@@ -162,10 +169,10 @@ __global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links
     const char* src = (const char*)in + r * in_stride;
     const BlockPos p = block_pos(g, blk);
 
-    cpx<R> acc[12];
+    cpx<R> acc[1][12];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = {(R)0, (R)0};
-    hopping_sum_ahead<PIN, PLINK, hops_in_flight<PIN>(), DAG>(g, p, l, src, links, acc);
+    for (int k = 0; k < 12; ++k) acc[0][k] = {(R)0, (R)0};
+    hopping_sum_ahead<PIN, PLINK, hops_in_flight<PIN>(), DAG, 1>(g, p, l, src, 0, links, acc);
 
     GlobalSpinor<PIN, DAG> ld{src, g.nblk};
     cpx<R> self[12], res[12];
@@ -175,7 +182,7 @@ __global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links
     clover_apply(cl, self, res);
     const R k = (R)kappa;
 #pragma unroll
-    for (int i = 0; i < 12; ++i) res[i] = {res[i].re - k * acc[i].re, res[i].im - k * acc[i].im};
+    for (int i = 0; i < 12; ++i) res[i] = {res[i].re - k * acc[0][i].re, res[i].im - k * acc[0][i].im};
     if (DAG) negate_lower(res);
     using RO = typename SpinorIO<POUT>::R;
     cpx<RO> o[12];
@@ -190,8 +197,8 @@ __global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links
     SpinorIO<POUT>::store((char*)out + r * out_stride, g.nblk, blk, l, o);
 }
 
-// Multi-right-hand-side variant: work item = (block, tile of right-hand
-// sides).  The block's links go to LDS once and its clover term to registers
+// Variant for several right-hand sides in FP64, and in FP32 for tiles of three
+// and more: work item = (block, tile of right-hand sides).  The block's links go to LDS once and its clover term to registers
 // once per item; every right-hand side of the tile reuses them.  Backward
 // links of neighbours outside the block come from HBM (cache).  With
 // gridDim.x < nitems the workgroups stride over the items (persistent).
@@ -333,6 +340,78 @@ __global__ CS_DSLASH_BOUNDS void k_dslash_tiled(Geom g, const void* __restrict__
     }
 }
 
+// Pairs in FP32 and any tile in the 16-bit formats: right-hand sides in groups
+// of G, a hop loading its link once for the group, the next hops' loads in
+// flight, and the clover term serving the group; nothing is staged in LDS and
+// no lane waits for another.  The same terms in the same order as k_dslash.
+// Bound by the chain of loads below a few rounds of workgroups and by HBM
+// above.  FP16, three right-hand sides: 12 x 20 x 28 x 36 66 us (one workgroup
+// each 81, staged tile 81), 32^3 x 64 431 (644, 604); FP32 pairs, 16^3 x 32 with
+// twelve 110 (172, staged tiles of four 134), 32^3 x 64 with two 463 (590).
+// FP32 tiles of three and more stay with the staged kernel: three spinors a hop
+// leave no registers for a hop ahead (32^3 x 64 with three: 727 us, as 2 + 1
+// 689, staged 650).
+template <int PIN, int G>
+constexpr int group_hops_in_flight() { return PIN == P_F32 ? (G == 1 ? 3 : 1) : (G == 3 ? 1 : G == 2 ? 2 : 3); }
+
+template <int G, int PIN, int POUT, int PLINK, bool DAG>
+__device__ __forceinline__ void dslash_group(const Geom& g, const BlockPos& p, int lane, const void* links,
+                                             const void* clover, float kappa, void* out, const void* in,
+                                             size_t in_stride, size_t out_stride) {
+    int l = lane;
+    asm volatile("" : "+v"(l));  // addresses are made here, not kept from group to group
+    cpx<float> acc[G][12];
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+#pragma unroll
+        for (int k = 0; k < 12; ++k) acc[j][k] = {0.f, 0.f};
+    hopping_sum_ahead<PIN, PLINK, group_hops_in_flight<PIN, G>(), DAG, G>(g, p, l, in, in_stride, links, acc);
+    float cl[72];
+    CloverIO<float>::template load<false>(clover, p.blk, l, cl);
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        GlobalSpinor<PIN, DAG> ld{(const char*)in + j * in_stride, g.nblk};
+        cpx<float> self[12], res[12];
+        ld.load(p.blk, l, self);
+        clover_apply(cl, self, res);
+#pragma unroll
+        for (int i = 0; i < 12; ++i)
+            res[i] = {res[i].re - kappa * acc[j][i].re, res[i].im - kappa * acc[j][i].im};
+        if (DAG) negate_lower(res);
+        SpinorIO<POUT>::store((char*)out + j * out_stride, g.nblk, p.blk, l, res);
+    }
+}
+
+// Work item = (block, tile of right-hand sides); the tiles of a block are
+// neighbours on one XCD, whose L2 serves their links and clover term.
+template <int PIN, int POUT, int PLINK, bool DAG>
+__global__ CS_DSLASH_BOUNDS void k_dslash_groups(Geom g, const void* links, const void* clover, double kappa,
+                                                 void* out, const void* in, size_t in_stride, size_t out_stride,
+                                                 int nrhs, int tile, int nitems) {
+    constexpr int GM = PIN == P_F32 ? 2 : 3;  // as many as leave two waves per SIMD
+    const int ntiles = (nrhs + tile - 1) / tile;
+    for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const int w = xcd_remap(item, nitems);
+        const int r0 = w % ntiles * tile, r1 = r0 + tile < nrhs ? r0 + tile : nrhs;
+        const BlockPos p = block_pos(g, block_of_item(g, w / ntiles));
+        auto go = [&](auto n, int r) {
+            dslash_group<decltype(n)::value, PIN, POUT, PLINK, DAG>(
+                g, p, threadIdx.x, links, clover, (float)kappa, (char*)out + (size_t)r * out_stride,
+                (const char*)in + (size_t)r * in_stride, in_stride, out_stride);
+        };
+        int r = r0;
+#pragma unroll 1
+        for (; r + GM <= r1; r += GM) go(std::integral_constant<int, GM>{}, r);
+        if constexpr (GM > 2) {
+            if (r + 2 <= r1) {
+                go(std::integral_constant<int, 2>{}, r);
+                r += 2;
+            }
+        }
+        if (r < r1) go(std::integral_constant<int, 1>{}, r);
+    }
+}
+
 template <int PIN, int POUT, int PLINK>
 hipError_t launch_tiled(const OpData& op, bool dagger, void* out, const void* in, int nrhs,
                         const LaunchCfg& cfg, hipStream_t s, const void* sub = nullptr) {
@@ -342,21 +421,31 @@ hipError_t launch_tiled(const OpData& op, bool dagger, void* out, const void* in
     const size_t is = spinor_bytes_per_site(PIN) * op.g.V, os = spinor_bytes_per_site(POUT) * op.g.V;
     const void* cl = PIN == P_F64 ? op.clover64 : op.clover32;
     const void* lk = op.links[PLINK];
-    auto go = [&](auto dag, auto with_sub) {
-        hipLaunchKernelGGL((k_dslash_tiled<PIN, POUT, PLINK, decltype(dag)::value, decltype(with_sub)::value>),
-                           dim3(grid), dim3(BLOCK_SITES), 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os, nrhs,
-                           tile, nitems);
-    };
-    if (sub) {
-        if constexpr (PIN == P_F64 && POUT == P_F64) {
-            if (dagger) go(std::true_type{}, std::true_type{});
-            else go(std::false_type{}, std::true_type{});
-        } else {
-            return hipErrorInvalidValue;
+    if constexpr (PIN != P_F64) {
+        if (sub) return hipErrorInvalidValue;
+        if (PIN != P_F32 || tile == 2) {
+            auto go = [&](auto dag) {
+                hipLaunchKernelGGL((k_dslash_groups<PIN, POUT, PLINK, decltype(dag)::value>), dim3(grid),
+                                   dim3(BLOCK_SITES), 0, s, op.g, lk, cl, op.kappa, out, in, is, os, nrhs, tile,
+                                   nitems);
+            };
+            dagger ? go(std::true_type{}) : go(std::false_type{});
+            return hipGetLastError();
         }
-    } else {
-        if (dagger) go(std::true_type{}, std::false_type{});
-        else go(std::false_type{}, std::false_type{});
+    }
+    if constexpr (PIN == P_F64 || PIN == P_F32) {
+        auto go = [&](auto dag, auto with_sub) {
+            hipLaunchKernelGGL((k_dslash_tiled<PIN, POUT, PLINK, decltype(dag)::value, decltype(with_sub)::value>),
+                               dim3(grid), dim3(BLOCK_SITES), 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os,
+                               nrhs, tile, nitems);
+        };
+        auto with_dag = [&](auto dag) {
+            if constexpr (PIN == P_F64 && POUT == P_F64) {
+                if (sub) return go(dag, std::true_type{});
+            }
+            go(dag, std::false_type{});
+        };
+        dagger ? with_dag(std::true_type{}) : with_dag(std::false_type{});
     }
     return hipGetLastError();
 }
@@ -383,42 +472,47 @@ hipError_t launch3(const OpData& op, bool dagger, void* out, const void* in, con
 
 }  // namespace
 
-// The tiled kernel against the one with a workgroup per block and right-hand
-// side, in tile_for's units: workgroups resident at a time, the load of a
-// tile's links and clover term, the cost of an odd tile, and what a full round
-// of the untiled kernel takes.  Fitted at 8^4 to 24^3 x 48 with 2 to 16
-// right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.  In FP64
-// sharing pays where links, clover term and a field leave the 256 MB cache
-// (24^3 x 48 with 12: 2.41 ms untiled, 2.03 in tiles of six; 16^3 x 32 with 5:
-// 151 us untiled, 157 in one tile).  Two workgroups per compute unit or less
-// have nothing to gain by sharing (8^4 with 12: 9 us untiled, 16 in tiles of
-// two).
+// The kernels for tiles against the one with a workgroup per block and
+// right-hand side, in tile_for's units: workgroups resident at a time, the load
+// of a staged tile's links and clover term, the cost of an odd staged tile,
+// what a round of the grouped kernel takes for two and for three right-hand
+// sides, and what a full round of the untiled kernel takes.  Fitted at 8^4 to
+// 32^3 x 64 with 2 to 16 right-hand sides; a unit is about 9 us below FP64 and
+// 14 us in FP64.  In FP64 sharing pays where links, clover term and a field
+// leave the 256 MB cache (24^3 x 48 with 12: 2.41 ms untiled, 2.03 in tiles of
+// six; 16^3 x 32 with 5: 151 us untiled, 157 in one tile).  Two workgroups per
+// compute unit or less have nothing to gain by sharing (8^4 with 12: 9 us
+// untiled, 11 in pairs).
 struct DslashModel {
     int slots;
     double head, odd;
+    double group2, group3;  // 0: tiles of that size are staged
     int untiled_slots;
     double untiled_units;
 };
 static DslashModel dslash_model(const Geom& g, int prec) {
-    if (prec == P_F64) return {256, 0.5, 0.0, 256, g.V * 1344 > (256ll << 20) ? 1.5 : 1.0};
-    if (prec == P_F32) return {512, 1.0, 0.6, 512, 1.65};
-    return {512, 1.0, 0.8, 1024, 2.45};
+    if (prec == P_F64) return {256, 0.5, 0.0, 0.0, 0.0, 256, g.V * 1344 > (256ll << 20) ? 1.5 : 1.0};
+    if (prec == P_F32) return {512, 1.0, 0.6, 2.6, 0.0, 512, 1.65};
+    return {512, 1.0, 0.8, 2.0, 2.6, 1024, 2.45};
 }
 
 double dslash_tile_units(const Geom& g, int prec, int nrhs, int t) {
     const DslashModel m = dslash_model(g, prec);
     if (t <= 1) return (double)(((long long)g.nblk * nrhs + m.untiled_slots - 1) / m.untiled_slots) * m.untiled_units;
     const long long wgs = (long long)g.nblk * ((nrhs + t - 1) / t);
-    return (double)((wgs + m.slots - 1) / m.slots) * (m.head + t + (t & 1 ? m.odd : 0.0));
+    double tile = m.head + t + (t & 1 ? m.odd : 0.0);
+    if (t == 2 && m.group2 > 0.0) tile = m.group2;
+    else if (m.group3 > 0.0) tile = t / 3 * m.group3 + (t % 3 == 2 ? m.group2 : t % 3 ? m.untiled_units : 0.0);
+    return (double)((wgs + m.slots - 1) / m.slots) * tile;
 }
 
 LaunchCfg dslash_default_cfg(const Geom& g, int prec, int nrhs) {
     LaunchCfg c;
-    const DslashModel m = dslash_model(g, prec);
     if (nrhs < 2 || (long long)g.nblk * nrhs <= 512) return c;
-    double units;
-    const int t = tile_for(g.nblk, nrhs, m.slots, m.head, m.odd, &units);
-    if (t > 1 && units < 0.95 * dslash_tile_units(g, prec, nrhs, 1)) c.rhs_tile = t;
+    int best = 2;
+    for (int t = 3; t <= nrhs && t <= 64; ++t)
+        if (dslash_tile_units(g, prec, nrhs, t) < dslash_tile_units(g, prec, nrhs, best)) best = t;
+    if (dslash_tile_units(g, prec, nrhs, best) < 0.95 * dslash_tile_units(g, prec, nrhs, 1)) c.rhs_tile = best;
     return c;
 }
 
