@@ -806,14 +806,14 @@ hipError_t launch_p(const OpData& op, int colour, int n_mr, int mode, void* x, c
 // launch shape is not chosen for a batch.  The lane-pair kernel halves the
 // dependent arithmetic of a block visit but fits one workgroup per compute
 // unit (the one-lane kernel fits two), so it pays only while a colour has at
-// most one block per compute unit (256 on MI355X): measured 7-10% faster at
-// 128 and 256 blocks per colour, 35% slower at 1296 and 4096.
+// most one block per compute unit (256 on MI355X): measured 7-8% faster at
+// 128 and 256 blocks per colour, 16% slower at 648 and 45% at 1296 and 4096.
 static int default_lanes_per_site(const Geom& g) { return g.nblk / 2 <= 256 ? 2 : 1; }
 
 // For a batch the line lies at 256 visits of a colour in all (blocks times
-// right-hand sides): at 16^3 x 32 one right-hand side takes 107 us a cycle pair
-// with lane pairs and 118 with one lane, two take 200 and 163, twelve 891 and
-// 687 in their best tiles.
+// right-hand sides): at 16^3 x 32 one right-hand side takes 103 us a cycle pair
+// with lane pairs and 111 with one lane, two take 172 and 168, twelve 861 and
+// 671 in their best tiles.
 int sap_default_lanes(const Geom& g, int prec, int nrhs, int block_solver) {
     if (prec == P_F64 || block_solver == BLOCK_EO) return 1;
     return (long long)(g.nblk / 2) * nrhs <= 256 ? 2 : 1;
