@@ -418,27 +418,24 @@ struct LaunchCfg {
     int lanes_per_site = 0;
 };
 
-// Tile of right-hand sides for a launch over `blocks` blocks with `slots`
-// workgroups on the GPU at a time, from a model that the measured times follow
-// to about 5 %: a workgroup takes head + tile units (head: what it loads once
-// for its tile; odd: what an odd tile costs on top where right-hand sides go
-// in pairs), and the launch as many rounds as the slots need for all
+// Tile of right-hand sides for a smoother launch over `blocks` blocks with
+// `slots` workgroups on the GPU at a time, from a model that the measured times
+// follow to about 5 %: a workgroup takes head + tile units (head: what it loads
+// once for its tile), and the launch as many rounds as the slots need for all
 // workgroups, so a tile that leaves a round nearly empty loses to one that
-// fills it (12 right-hand sides of 512 blocks in 512 slots: tiles of 4 and 8
-// take 135 and 153 us for the FP32 operator, 6 and 12 take 125 and 117).
-// *units: the model's time.
-inline int tile_for(long long blocks, int nrhs, int slots, double head, double odd, double* units) {
+// fills it (FP32 smoother, 12 right-hand sides of 256 blocks a colour in 512
+// slots: tiles of 4 and 8 take 735 and 852 us, 3 and 6 take 679 and 671).
+inline int tile_for(long long blocks, int nrhs, int slots, double head) {
     int best = 1;
     double least = 0;
     for (int t = 1; t <= nrhs && t <= 64; ++t) {
         const long long wgs = blocks * ((nrhs + t - 1) / t);
-        const double u = (double)((wgs + slots - 1) / slots) * (head + t + (t & 1 ? odd : 0.0));
+        const double u = (double)((wgs + slots - 1) / slots) * (head + t);
         if (t == 1 || u < least) {
             least = u;
             best = t;
         }
     }
-    if (units) *units = least;
     return best;
 }
 
@@ -449,7 +446,7 @@ hipError_t launch_dslash_tiled(const OpData& op, int prec, bool dagger, void* ou
 // Launch shape of nrhs right-hand sides when the caller names none (rhs_tile
 // 1: one workgroup per block and right-hand side, the untiled kernel).
 LaunchCfg dslash_default_cfg(const Geom& g, int prec, int nrhs);
-// Units (tile_for's model) of the tiled launch at rhs_tile t.
+// Units (rounds of workgroups times what one takes) of the launch at rhs_tile t.
 double dslash_tile_units(const Geom& g, int prec, int nrhs, int t);
 
 // The same batched launch from FP32 input (FP32 links) into FP16 or BF16

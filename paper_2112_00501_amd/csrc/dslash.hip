@@ -473,12 +473,11 @@ hipError_t launch3(const OpData& op, bool dagger, void* out, const void* in, con
 }  // namespace
 
 // The kernels for tiles against the one with a workgroup per block and
-// right-hand side, in tile_for's units: workgroups resident at a time, the load
-// of a staged tile's links and clover term, the cost of an odd staged tile,
-// what a round of the grouped kernel takes for two and for three right-hand
-// sides, and what a full round of the untiled kernel takes.  Fitted at 8^4 to
-// 32^3 x 64 with 2 to 16 right-hand sides; a unit is about 9 us below FP64 and
-// 14 us in FP64.  In FP64 sharing pays where links, clover term and a field
+// right-hand side, as rounds of resident workgroups times what a round takes:
+// a staged tile its links and clover term (head), a unit per right-hand side and
+// what an odd one costs on top; the grouped kernel for two and for three
+// right-hand sides; the untiled kernel.  Fitted at 8^4 to 32^3 x 64 with 2 to 16
+// right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.  In FP64 sharing pays where links, clover term and a field
 // leave the 256 MB cache (24^3 x 48 with 12: 2.41 ms untiled, 2.03 in tiles of
 // six; 16^3 x 32 with 5: 151 us untiled, 157 in one tile).  Two workgroups per
 // compute unit or less have nothing to gain by sharing (8^4 with 12: 9 us

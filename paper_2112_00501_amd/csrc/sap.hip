@@ -836,7 +836,7 @@ LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver) {
     // the FP64 kernel keeps nothing of the block between right-hand sides, and
     // the even-odd one is bound by its arithmetic with one workgroup per unit
     if (nrhs > 1 && prec != P_F64 && block_solver != BLOCK_EO)
-        c.rhs_tile = tile_for(g.nblk / 2, nrhs, SAP_SLOTS[c.lanes_per_site], SAP_HEAD, 0.0, nullptr);
+        c.rhs_tile = tile_for(g.nblk / 2, nrhs, SAP_SLOTS[c.lanes_per_site], SAP_HEAD);
     return c;
 }
 
