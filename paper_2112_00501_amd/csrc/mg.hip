@@ -210,18 +210,22 @@ __global__ __launch_bounds__(TPB) void k_mg_orthonormalize(Geom g, char* P, size
 //
 // Every block of D_c is a contraction over the sites and components of an
 // aggregate (self) or a face, so it runs on the matrix cores in FP32
-// (v_mfma_f32_16x16x4_f32).  A lane of a wave is (column j = lane % 16, site
-// lane / 16 of four): it loads its column's null vector at its site and the
-// neighbours, applies D to the two chirality halves, and then holds exactly
+// (v_mfma_f32_16x16x4_f32).  While D is applied a lane of a wave is (site
+// lane % 4 of the step, column lane / 4), so that four lanes read 64 consecutive
+// bytes of their column's null vector: it loads the vector at its site and the
+// neighbours and applies D to the two chirality halves.  The vector and the two
+// results then change lanes to (column lane % 16, site lane / 16) and are exactly
 // the operands of the products, the vector itself as row j of P^dag and D p as
-// column j, for four sites and one component at a time; nothing is transposed
-// or reduced across lanes.  Workgroup = (aggregate, 16 columns j of either
-// chirality): first the self term, a quarter of the sites per wave, summed over
-// the waves in LDS; then the faces, wave mu the -mu face.  RT row tiles of 16 cover nv
-// (rows and columns past nv repeat field nv - 1 and are not stored).
+// column j, for four sites and one component at a time; nothing is reduced
+// across lanes.  (Loading in the products' lane order needs no such change, but
+// sixteen neighbouring lanes then read sixteen vectors, 16 bytes each: 404 us at
+// 16^3 x 32 with 16 vectors, 362 now.)  Workgroup = (aggregate, 16 columns j of
+// either chirality): first the self term, a quarter of the sites per wave, summed
+// over the waves in LDS; then the faces, wave mu the -mu face.  RT row tiles of 16
+// cover nv (rows and columns past nv repeat field nv - 1 and are not stored).
 // Per site and column about 1400 VALU instructions apply D and 96 products of
-// 32 cycles contract; with one column per workgroup and dot products reduced
-// through LDS the same work took 17.6 ms at 32^3 x 64 with 16 vectors.
+// 32 cycles contract: 5.9 ms at 32^3 x 64 with 16 vectors; with one column per
+// workgroup and dot products reduced through LDS the same work took 17.6 ms.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // y0 += (1 + S gamma_mu) U' psi_0, y1 += (1 + S gamma_mu) U' psi_1 for the
@@ -333,6 +337,15 @@ __device__ __forceinline__ void asm_products(const cpx<float>* q, const cpx<floa
         }
 }
 
+// Lane site + 4 column -> lane column + 16 site, for twelve values
+__device__ __forceinline__ void asm_turn(cpx<float>* v) {
+    const int lane = threadIdx.x & 63, src = 4 * ((lane >> 4) + 4 * (lane & 15));
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        v[k] = {__int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v[k].re))),
+                __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v[k].im)))};
+}
+
 template <int RT>
 __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, const void* links, const void* clover,
                                                                       float kappa, const char* P, size_t fs, int nv,
@@ -341,10 +354,12 @@ __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, co
     const BlockPos p = block_pos(g, blk);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, kk = lane >> 4;
     const int col = 16 * ct + j;
-    const char* Pj = P + (size_t)(col < nv ? col : nv - 1) * fs;
-    const char* Pi[RT];  // the rows this lane supplies
+    // while D is applied: column lj, site lk of the step
+    const int lj = lane >> 2, lk = lane & 3;
+    const char* Pj = P + (size_t)(16 * ct + lj < nv ? 16 * ct + lj : nv - 1) * fs;
+    const char* Pi[RT];  // the rows this lane loads
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) Pi[rt] = P + (size_t)(16 * rt + j < nv ? 16 * rt + j : nv - 1) * fs;
+    for (int rt = 0; rt < RT; ++rt) Pi[rt] = P + (size_t)(16 * rt + lj < nv ? 16 * rt + lj : nv - 1) * fs;
     AsmTile acc[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) asm_clear(acc[rt]);
@@ -359,7 +374,7 @@ __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, co
     // x rows, so that the waves' neighbours meet in the L1
 #pragma unroll 1
     for (int s = 0; s < 16; ++s) {
-        const int l = kk + 4 * wave + 16 * s;
+        const int l = lk + 4 * wave + 16 * s;
         cpx<float> q[12], y0[12], y1[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) y0[k] = y1[k] = {0.f, 0.f};
@@ -380,9 +395,12 @@ __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, co
             y0[k] = {fmaf(-kappa, y0[k].re, c0.re), fmaf(-kappa, y0[k].im, c0.im)};
             y1[k] = {fmaf(-kappa, y1[k].re, c1.re), fmaf(-kappa, y1[k].im, c1.im)};
         }
+        asm_turn(y0);
+        asm_turn(y1);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             if (RT > 1) SpinorIO<P_F32>::load(Pi[rt], g.nblk, blk, l, q);
+            asm_turn(q);
             asm_products(q, y0, y1, acc[rt]);
         }
     }
@@ -413,8 +431,8 @@ __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, co
 #pragma unroll 1
     for (int s = 0; s < 16; ++s) {
         const int lo = s & 3, hi = s >> 2;
-        const int l = mu == 0 ? 4 * kk + 16 * lo + 64 * hi : mu == 1 ? kk + 16 * lo + 64 * hi
-                      : mu == 2 ? kk + 4 * lo + 64 * hi : kk + 4 * lo + 16 * hi;
+        const int l = mu == 0 ? 4 * lk + 16 * lo + 64 * hi : mu == 1 ? lk + 16 * lo + 64 * hi
+                      : mu == 2 ? lk + 4 * lo + 64 * hi : lk + 4 * lo + 16 * hi;
         cpx<float> y0[12], y1[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) y0[k] = y1[k] = {0.f, 0.f};
@@ -429,10 +447,13 @@ __global__ __launch_bounds__(TPB, RT == 1 ? 2 : 1) void k_mg_assemble(Geom g, co
             y0[k] = {-kappa * y0[k].re, -kappa * y0[k].im};
             y1[k] = {-kappa * y1[k].re, -kappa * y1[k].im};
         }
+        asm_turn(y0);
+        asm_turn(y1);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             cpx<float> q[12];
             SpinorIO<P_F32>::load(Pi[rt], g.nblk, blk, l, q);
+            asm_turn(q);
             asm_products(q, y0, y1, acc[rt]);
         }
     }
