@@ -164,7 +164,8 @@ int cs_apply_Ddag(cs_gauge g, cs_clover c, cs_prec prec, void* out, const void* 
  * that many workgroups striding over the (block, tile) work items; and
  * lanes_per_site of the FP32 / FP16 / BF16 SAP kernel: 1 (one lane per site),
  * 2 (a lane pair per site: forward and backward hops on separate lanes, one
- * chirality each), or 0 (the library chooses from the number of blocks).
+ * chirality each; the two differ in rounding), or 0 (the library chooses from
+ * the number of blocks, whatever nrhs is).
  * Values other than 0, 1, 2 mean 0; the operator ignores lanes_per_site and
  * FP64 SAP always uses one lane per site. */
 typedef struct {
@@ -202,8 +203,9 @@ int cs_sap_smooth(cs_gauge g, cs_clover c, cs_prec prec, void* x, const void* b,
 
 /* cs_sap_smooth and cs_apply_D with an explicit multi-right-hand-side launch
  * shape (cfg NULL: the library chooses from the lattice and nrhs, as
- * cs_sap_smooth and cs_apply_D do).  Results are bitwise identical to the
- * calls without one; lanes_per_site, where given, must be theirs. */
+ * cs_sap_smooth and cs_apply_D do).  With equal lanes per site (0 or those the
+ * library chooses) every right-hand side's result is bitwise that of its own
+ * call without one. */
 int cs_sap_smooth_cfg(cs_gauge g, cs_clover c, cs_prec prec, void* x, const void* b,
                       int n_cy, int n_mr, int x0_is_zero, int nrhs,
                       const cs_launch_config* cfg, void* stream);

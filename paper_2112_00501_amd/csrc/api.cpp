@@ -389,8 +389,7 @@ static int sap_common(cs_gauge g, cs_clover c, cs_prec prec, void* x, const void
     const size_t bytes = cs::spinor_bytes_per_site(prec) * (size_t)g->g.V * nrhs;
     if (overlap(b, x, bytes)) return fail(CS_ERR_INVALID, "x and b overlap");
     const cs::OpData op = make_op(g, c);
-    cs::LaunchCfg lc = cfg ? to_cfg(cfg) : cs::sap_default_cfg(g->g, prec, nrhs, solver);
-    if (lc.lanes_per_site == 0) lc.lanes_per_site = cs::sap_default_lanes(g->g, prec, nrhs, solver);
+    const cs::LaunchCfg lc = cfg ? to_cfg(cfg) : cs::sap_default_cfg(g->g, prec, nrhs, solver);
     hipStream_t s = (hipStream_t)stream;
     if (n_cy == 0 && x0_is_zero) {
         CS_HIP(hipMemsetAsync(x, 0, bytes, s));
@@ -453,7 +452,8 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
     // Candidates: the tiles whose model time is within 12 % of the least (the
     // model leaves out caches and clocks; 1 always), as a grid of all work
     // items and as a persistent one, and for the smoother one and two lanes
-    // per site while both can be the faster (sap_default_lanes).
+    // per site while both can be the faster (past 512 visits of a colour one
+    // lane always was).
     struct Cand {
         int kind;  // 0: smoother, 1: operator
         cs::LaunchCfg lc;

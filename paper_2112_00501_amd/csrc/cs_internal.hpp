@@ -463,10 +463,10 @@ enum { BLOCK_MR = 0, BLOCK_JACOBI = 1, BLOCK_EO = 2 };
 hipError_t launch_sap_halfsweep(const OpData& op, int prec, int colour, int n_block, int mode,
                                 void* x, const void* b, int nrhs, const LaunchCfg& cfg, hipStream_t s,
                                 int block_solver = BLOCK_MR);
-// Launch shape of nrhs right-hand sides when the caller names none, and the
-// lanes per site it implies for any tile.
-LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver);
-int sap_default_lanes(const Geom& g, int prec, int nrhs, int block_solver);
+// Launch shape of nrhs right-hand sides when the caller names none (with the
+// lanes per site given, if any), and lanes per site when the launch shape has 0.
+LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver, int lanes = 0);
+int sap_default_lanes(const Geom& g, int prec, int block_solver);
 // Units (tile_for's model) of a half-sweep with that tile and those lanes.
 double sap_tile_units(const Geom& g, int nrhs, int t, int lanes);
 // sap_pair.hip: the same half-sweep with two lanes per site (FP32, FP16, BF16).

@@ -33,7 +33,12 @@ namespace {
 // n_cy SAP cycles on D x = b for nrhs FP32 fields; x0_zero: x starts at zero
 hipError_t sap_cycles(const OpData& op, int n_cy, int n_mr, bool x0_zero, void* x, const void* b, int nrhs,
                       hipStream_t s) {
-    const LaunchCfg cfg = sap_default_cfg(op.g, P_F32, nrhs, BLOCK_MR);
+    // lane pairs while a colour has at most one visit per compute unit in all
+    // (for one field the default); the setup's batches past that take the faster
+    // one-lane kernel on any lattice (16^3 x 32, 16 vectors: 11.4 ms, 13.3 with
+    // lane pairs), since their smoothed fields leave the library only as P and D_c
+    const int lanes = (long long)(op.g.nblk / 2) * nrhs <= 256 ? 2 : 1;
+    const LaunchCfg cfg = sap_default_cfg(op.g, P_F32, nrhs, BLOCK_MR, lanes);
     for (int cy = 0; cy < n_cy; ++cy)
         for (int col = 0; col < 2; ++col) {
             const int mode = (x0_zero && cy == 0) ? (col == 0 ? 1 : 2) : 0;
@@ -131,7 +136,8 @@ struct PassWork {
 // restriction of all of them, the coarse solves of all of them side by side
 // (one launch per step of the solver, D_c read once for four), one
 // prolongation of all, and the post-smoothing as one batched SAP launch per
-// half-sweep (the results are those of M_MG applied to each v_i in turn).
+// half-sweep (the results are those of M_MG applied to each v_i in turn, up to
+// the rounding of the smoother's kernel).
 // The coarse iterations run in chunks until the host sees every solve stopped.
 hipError_t adaptive_pass(const OpData& op, MgData& m, const PassWork& w, hipStream_t s) {
     const int nv = m.p.nv, cap = m.p.n_coarse;

@@ -802,21 +802,19 @@ hipError_t launch_p(const OpData& op, int colour, int n_mr, int mode, void* x, c
 
 }  // namespace
 
-// Lanes per site when the caller leaves the choice to the library and the
-// launch shape is not chosen for a batch.  The lane-pair kernel halves the
-// dependent arithmetic of a block visit but fits one workgroup per compute
-// unit (the one-lane kernel fits two), so it pays only while a colour has at
-// most one block per compute unit (256 on MI355X): measured 7-8% faster at
-// 128 and 256 blocks per colour, 16% slower at 648 and 45% at 1296 and 4096.
-static int default_lanes_per_site(const Geom& g) { return g.nblk / 2 <= 256 ? 2 : 1; }
-
-// For a batch the line lies at 256 visits of a colour in all (blocks times
-// right-hand sides): at 16^3 x 32 one right-hand side takes 103 us a cycle pair
-// with lane pairs and 111 with one lane, two take 172 and 168, twelve 861 and
-// 671 in their best tiles.
-int sap_default_lanes(const Geom& g, int prec, int nrhs, int block_solver) {
-    if (prec == P_F64 || block_solver == BLOCK_EO) return 1;
-    return (long long)(g.nblk / 2) * nrhs <= 256 ? 2 : 1;
+// Lanes per site when the caller leaves the choice to the library.  The
+// lane-pair kernel halves the dependent arithmetic of a block visit but fits
+// one workgroup per compute unit (the one-lane kernel fits two), so it pays
+// only while a colour has at most one block per compute unit (256 on
+// MI355X): measured 7-8% faster at 128 and 256 blocks per colour, 16% slower
+// at 648 and 45% at 1296 and 4096.  The line is drawn by the lattice alone,
+// although a batch past 256 visits of a colour is faster with one lane
+// (16^3 x 32, twelve right-hand sides, a cycle pair in their best tiles: 861 us
+// and 671): the kernels sum in different orders, and a right-hand side keeps
+// the result of its own call whatever it is batched with.
+int sap_default_lanes(const Geom& g, int prec, int block_solver) {
+    if (prec == P_F64 || block_solver == BLOCK_EO) return 1;  // have the one-lane form only
+    return g.nblk / 2 <= 256 ? 2 : 1;
 }
 
 // Workgroups resident at a time and the cost of a tile's links and clover
@@ -830,9 +828,9 @@ double sap_tile_units(const Geom& g, int nrhs, int t, int lanes) {
     return (double)((wgs + SAP_SLOTS[lanes] - 1) / SAP_SLOTS[lanes]) * (SAP_HEAD + t);
 }
 
-LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver) {
+LaunchCfg sap_default_cfg(const Geom& g, int prec, int nrhs, int block_solver, int lanes) {
     LaunchCfg c;
-    c.lanes_per_site = sap_default_lanes(g, prec, nrhs, block_solver);
+    c.lanes_per_site = lanes > 0 ? lanes : sap_default_lanes(g, prec, block_solver);
     // the FP64 kernel keeps nothing of the block between right-hand sides, and
     // the even-odd one is bound by its arithmetic with one workgroup per unit
     if (nrhs > 1 && prec != P_F64 && block_solver != BLOCK_EO)
@@ -847,8 +845,7 @@ hipError_t launch_sap_halfsweep(const OpData& op, int prec, int colour, int n_mr
     // differ from those of the two half-sweeps that start from x = 0
     ProfScope pm(mode == 0 ? "sap_general" : "sap_from_zero", s);
     if (bs != BLOCK_MR && bs != BLOCK_JACOBI && bs != BLOCK_EO) return hipErrorInvalidValue;
-    const int lanes = cfg.lanes_per_site > 0 ? cfg.lanes_per_site : default_lanes_per_site(op.g);
-    // the even-odd block solver has the one-lane form only
+    const int lanes = cfg.lanes_per_site > 0 ? cfg.lanes_per_site : sap_default_lanes(op.g, prec, bs);
     if (lanes == 2 && prec != P_F64 && bs != BLOCK_EO)
         return launch_sap_pair(op, prec, colour, n_mr, mode, x, b, nrhs, cfg, s, bs);
     switch (prec) {
