@@ -159,18 +159,14 @@ struct SpinorIO<P_BF16> : SpinorIO16<P_BF16> {};
 // ---------------------------------------------------------------------- links
 
 // Row 2 of an SU(3) matrix from rows 0 and 1: conj(row0 x row1).  The
-// roundings are spelled out (one product, then three FMA), so that every
-// kernel rebuilds the same bits whatever the compiler contracts around it.
+// roundings are spelled out (each complex product a product and an FMA, then
+// their difference), so that every kernel rebuilds the same bits whatever the
+// compiler contracts around it.
 template <typename R>
 __device__ __forceinline__ cpx<R> conj_minor(cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d) {  // conj(a b - c d)
-    R re = a.re * b.re, im = -(a.re * b.im);
-    re = fma(-a.im, b.im, re);
-    im = fma(-a.im, b.re, im);
-    re = fma(-c.re, d.re, re);
-    im = fma(c.re, d.im, im);
-    re = fma(c.im, d.im, re);
-    im = fma(c.im, d.re, im);
-    return {re, im};
+    const R pr = fma(a.re, b.re, -(a.im * b.im)), pi = fma(a.im, b.re, a.re * b.im);
+    const R qr = fma(c.re, d.re, -(c.im * d.im)), qi = fma(c.im, d.re, c.re * d.im);
+    return {pr - qr, qi - pi};
 }
 template <typename R>
 __device__ __forceinline__ void su3_row2(cpx<R>* u) {
