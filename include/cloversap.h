@@ -273,8 +273,14 @@ typedef struct {
                              (kept with the clover handle), private stream and
                              host thread, so the memory-bound level-1 kernels
                              of one group overlap the smoother of another.
-                             Every column's result is bit-identical to its
-                             single-right-hand-side solve either way.         */
+                             Either way, with rhs_tile >= 1 every column's
+                             result is bit-identical to its
+                             single-right-hand-side solve.  With rhs_tile 0
+                             the autotuner measures the lanes per site too,
+                             and where it takes others than the lone solve
+                             (lattices of up to 256 blocks a colour), the
+                             smoother rounds differently and columns agree
+                             with their lone solves within the tolerance.     */
 } cs_solver_params;
 
 typedef struct {
@@ -298,7 +304,8 @@ void cs_solver_params_default(cs_solver_params* p);
  * x holds x0 on entry.  The right-hand sides advance together through
  * batched SAP and operator launches (links and clover read once per tile of
  * right-hand sides); each keeps its own scalars and stopping decisions, so
- * every column follows the iterations of a single-right-hand-side solve.
+ * every column follows the iterations of a single-right-hand-side solve (to
+ * the bit with params.rhs_tile >= 1, see rhs_groups).
  * stats (host, may be NULL) has nrhs entries; seconds is the wall time of the
  * whole call.  Device workspace (2 m nrhs fields plus scalars) is allocated on
  * first use and kept with the clover handle.  The work runs on a private
