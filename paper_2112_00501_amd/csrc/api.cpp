@@ -449,11 +449,12 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     hipError_t err = cs::blas_fill_pattern(bc, prec, bb, s);
-    // Candidates: the tiles whose model time is within 12 % of the least (the
-    // model leaves out caches and clocks; 1 always), as a grid of all work
-    // items and as a persistent one, and for the smoother one and two lanes
-    // per site while both can be the faster (past 512 visits of a colour one
-    // lane always was).
+    // Candidates: tile 1 and the three best by the model among those within
+    // 12 % of the least (the model leaves out caches and clocks), as a grid of
+    // all work items and as a persistent one, and for the smoother one and two
+    // lanes per site while both can be the faster (past 512 visits of a colour
+    // one lane always was).  The model does not fit the FP64 smoother, which
+    // keeps nothing between right-hand sides: a spread of tiles there.
     struct Cand {
         int kind;  // 0: smoother, 1: operator
         cs::LaunchCfg lc;
@@ -466,10 +467,19 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
                 return kind == 0 ? cs::sap_tile_units(g->g, nrhs, t, lanes) : cs::dslash_tile_units(g->g, prec, nrhs, t);
             };
             const int most = nrhs < 64 ? nrhs : 64;
-            double least = units(1);
-            for (int t = 2; t <= most; ++t) least = std::min(least, units(t));
-            for (int t = 1; t <= most; ++t) {
-                if (t > 1 && units(t) > 1.12 * least) continue;
+            std::vector<int> tiles;
+            if (kind == 0 && prec == CS_F64) {
+                for (int t : {4, 8, 12})
+                    if (t <= nrhs) tiles.push_back(t);
+            } else {
+                std::vector<std::pair<double, int>> ranked;
+                for (int t = 1; t <= most; ++t) ranked.emplace_back(units(t), t);
+                std::sort(ranked.begin(), ranked.end());
+                for (const auto& [u, t] : ranked)
+                    if (t > 1 && u <= 1.12 * ranked[0].first && tiles.size() < 3) tiles.push_back(t);
+            }
+            tiles.push_back(1);
+            for (int t : tiles)
                 for (int pw : {0, 2 * cus}) {
                     Cand c{kind, {}};
                     c.lc.rhs_tile = t;
@@ -477,7 +487,6 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
                     c.lc.lanes_per_site = kind == 0 ? lanes : 0;
                     cands.push_back(c);
                 }
-            }
         }
     float best_s = 1e30f, best_dd = 1e30f;
     cs::LaunchCfg bs, bd;
