@@ -63,17 +63,22 @@ void trim(Cache& c, int dev, size_t most) {
     }
 }
 
-// Waits for all work on the current device, dev, and marks its kept blocks
-// quiet.  hipFree is what waits: hipDeviceSynchronize would invalidate a
-// stream capture that another thread has open.  The caller holds the lock.
+// Waits for all work on dev and marks its kept blocks quiet.  hipFree is what
+// waits: hipDeviceSynchronize would invalidate a stream capture that another
+// thread has open.  The caller holds the lock.  A failure (device memory full)
+// is the caller's to act on and not left behind for its next launch check.
 hipError_t wait_for_device(Cache& c, int dev) {
+    OnDevice on(dev);
     void* q = nullptr;
     hipError_t e = hipMalloc(&q, 256);
     if (e == hipSuccess) e = hipFree(q);
-    if (e == hipSuccess)
-        for (Block& b : c.kept)
-            if (b.dev == dev) b.quiet = true;
-    return e;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    for (Block& b : c.kept)
+        if (b.dev == dev) b.quiet = true;
+    return hipSuccess;
 }
 
 }  // namespace
