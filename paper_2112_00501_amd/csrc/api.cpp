@@ -272,6 +272,7 @@ int cs_gauge_create(cs_lattice lat, const void* U, void* stream, cs_gauge* out) 
 
 int cs_gauge_destroy(cs_gauge g) {
     if (!g) return ok();
+    cs::dev_wait(g->links[0]);
     for (int p = 0; p < 4; ++p)
         if (g->links[p]) cs::dev_free(g->links[p]);
     delete g;
@@ -306,6 +307,7 @@ int cs_clover_create(cs_gauge g, double kappa, double csw, void* stream, cs_clov
 
 int cs_clover_destroy(cs_clover c) {
     if (!c) return ok();
+    cs::dev_wait(c->c64);
     c->work.reset();
     c->group_work.clear();
     if (c->force_H) cs::dev_free(c->force_H);

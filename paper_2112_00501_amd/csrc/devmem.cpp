@@ -149,6 +149,23 @@ void dev_free(void* p) {
     trim(c, b.dev, limit);
 }
 
+void dev_wait(const void* p) {
+    if (!p) return;
+    Cache& c = cache();
+    std::lock_guard<std::mutex> lk(c.mu);
+    auto it = c.live.find(const_cast<void*>(p));
+    if (it == c.live.end()) return;
+    const int dev = it->second.dev;
+    if (wait_for_device(c, dev) == hipSuccess) return;
+    // no memory left for the wait: returning kept blocks waits too
+    if (c.kept_bytes[dev] > 0) {
+        trim(c, dev, 0);
+    } else {
+        OnDevice on(dev);
+        (void)hipDeviceSynchronize();
+    }
+}
+
 void dev_lattice_created() {
     Cache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);

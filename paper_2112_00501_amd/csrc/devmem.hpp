@@ -17,6 +17,8 @@
 //     longest-kept blocks are freed first, and everything kept is freed as
 //     soon as no lattice handle exists, or when an allocation fails (which is
 //     then tried again);
+//   * destroying a handle waits for the device (dev_wait), as the hipFree calls
+//     did: what a caller queued with the handle has run when it is gone;
 //   * contents are not cleared, as with hipMalloc.
 // All calls may be made from any thread.
 #pragma once
@@ -29,6 +31,10 @@ namespace cs {
 
 hipError_t dev_alloc(void** p, size_t bytes);
 void dev_free(void* p);  // p may be null
+
+// Waits for all work on the device that the block p (handed out, or null)
+// belongs to.
+void dev_wait(const void* p);
 
 // Lattice handles alive (a handle is created / destroyed): blocks are kept
 // only while there is one.

@@ -130,11 +130,26 @@ static int failed_wait() {  // no error is left for the caller's next launch che
     CHECK(hipGetLastError() == hipSuccess);
     return 0;
 }
+static int wait() {  // by the probe's free, else by returning kept blocks, else by the device itself
+    void *a, *b;
+    CHECK(dev_alloc(&a, 40) == hipSuccess && dev_alloc(&b, 50) == hipSuccess);
+    for (int k = 0; k < 3; ++k) {
+        full = k > 0;
+        if (k == 1) dev_free(b);
+        pending = true;
+        dev_wait(a);
+        CHECK(!pending && hipGetLastError() == hipSuccess);
+    }
+    CHECK(used == 40);
+    dev_wait(nullptr);
+    return 0;
+}
 
 int main(int, char** v) {
     dev_lattice_created();
     struct { const char* name; int (*f)(); } all[] = {
         {"reuse", reuse}, {"bound", bound}, {"retry", retry}, {"last_lattice", last_lattice}, {"failed_wait", failed_wait},
+        {"wait", wait},
     };
     for (auto& t : all)
         if (!std::strcmp(t.name, v[1])) return t.f();
@@ -155,7 +170,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["reuse", "bound", "retry", "last_lattice", "failed_wait"])
+@pytest.mark.parametrize("case", ["reuse", "bound", "retry", "last_lattice", "failed_wait", "wait"])
 def test_pool(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout

@@ -1,0 +1,42 @@
+"""Destroying a handle waits for the work queued with it."""
+import pytest
+import torch
+
+from paper_2112_00501_amd import cloversap as cs
+from paper_2112_00501_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+DIMS = (16, 16, 16, 16)
+
+
+@pytest.fixture(scope="module")
+def links():
+    U = torch.from_numpy(synth.gauge_field(DIMS, 0.3, 151)).cuda()
+    torch.cuda.synchronize()
+    return U
+
+
+@pytest.mark.parametrize("handle", ["clover", "gauge", "multigrid"])
+def test_destroy_waits_for_queued_work(links, handle):
+    lat = cs.Lattice(DIMS)
+    op = cs.Operator(lat, links, 0.13, 1.0)
+    b = lat.new_field(cs.F32)
+    b.view(torch.float32).normal_()
+    x = lat.new_field(cs.F32)
+    mg = cs.Multigrid(op, torch.cat([b] * 4), cs.MgParams(nv=4, n_adapt=0)) if handle == "multigrid" else None
+    s, done = torch.cuda.Stream(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        op.sap_smooth(x, b, cs.F32, 500, 4, True)  # a thousand half-sweeps, tens of microseconds each
+        done.record(s)
+    assert not done.query()
+    if handle == "clover":
+        del op.clover
+    elif handle == "multigrid":
+        del mg
+    else:
+        # the clover handle holds the links' handle through its binding only
+        cs._lib.cs_gauge_destroy(op.gauge.handle)
+        op.gauge.handle = None
+    assert done.query()
