@@ -13,10 +13,10 @@
  *   cs_clover   C = 1 + T for one (kappa, c_sw), stored on the device as two
  *               6x6 Hermitian blocks per site
  * Handles are owned by the library and released with the matching destroy
- * call.  Spinor fields are caller-owned device buffers (for example torch
- * tensors) in the library's internal layout; cs_field_bytes() gives their
- * size and cs_field_import / cs_field_export convert from / to the
- * canonical layout below.
+ * call (see cs_release_cached_memory for their device memory).  Spinor fields
+ * are caller-owned device buffers (for example torch tensors) in the library's
+ * internal layout; cs_field_bytes() gives their size and cs_field_import /
+ * cs_field_export convert from / to the canonical layout below.
  *
  * Canonical layouts (complex double, interleaved re/im, site index x fastest:
  * s = x + Lx*(y + Ly*(z + Lz*t)), directions mu = 0..3 for x, y, z, t):
@@ -99,6 +99,16 @@ const char* cs_strerror(int status);
  * flag bits: CS_ERR_INVALID. */
 int cs_lattice_create(const int dims[4], const int block[4], int flags, cs_lattice* out);
 int cs_lattice_destroy(cs_lattice lat);
+
+/* The destroy calls of gauge, clover and multigrid handles wait until the
+ * device has finished all queued work.  The handle's device memory is kept by
+ * the library for later handles and workspaces of the same sizes, up to 1/16
+ * of the device's memory (18 GB of 288 GB) with the longest-kept blocks freed
+ * first, until the last lattice handle is destroyed or an allocation of the
+ * library fails.  This call returns all of it to the device at once, for a
+ * caller whose own allocator runs short. */
+int cs_release_cached_memory(void);
+
 /* Number of sites V. */
 long long cs_lattice_volume(cs_lattice lat);
 /* Bytes of one internal-layout spinor field of precision prec holding nrhs

@@ -60,7 +60,7 @@ class _Stats(C.Structure):
 _lib = None
 
 EXPORTED = ["cs_last_error", "cs_strerror", "cs_lattice_create", "cs_lattice_destroy",
-            "cs_lattice_volume", "cs_field_bytes", "cs_field_import", "cs_field_export",
+            "cs_release_cached_memory", "cs_lattice_volume", "cs_field_bytes", "cs_field_import", "cs_field_export",
             "cs_gauge_create", "cs_gauge_destroy", "cs_clover_create", "cs_clover_destroy",
             "cs_clover_export", "cs_clover_inverse_export", "cs_apply_D", "cs_apply_Ddag",
             "cs_apply_D_cfg", "cs_sap_smooth", "cs_sap_smooth_cfg", "cs_sap_smooth_jacobi", "cs_sap_smooth_eo",
@@ -89,6 +89,7 @@ def load_library(path: str = LIB_PATH):
     L.cs_strerror.argtypes = [I]
     L.cs_lattice_create.argtypes = [C.POINTER(C.c_int), C.POINTER(C.c_int), I, C.POINTER(P)]
     L.cs_lattice_destroy.argtypes = [P]
+    L.cs_release_cached_memory.argtypes = []
     L.cs_lattice_volume.argtypes = [P]
     L.cs_lattice_volume.restype = C.c_longlong
     L.cs_field_bytes.argtypes = [P, I, I]
@@ -547,6 +548,13 @@ def profile_enable(on: bool = True):
 
 def profile_reset():
     _check(_lib.cs_profile_reset(), "cs_profile_reset")
+
+
+def release_cached_memory():
+    """Return the device memory that destroyed handles left with the library
+    (kept for later handles while any Lattice lives)."""
+    load_library()
+    _check(_lib.cs_release_cached_memory(), "cs_release_cached_memory")
 
 
 def device_copy(dst: torch.Tensor, src: torch.Tensor, stream=None):

@@ -225,6 +225,11 @@ int cs_lattice_destroy(cs_lattice lat) {
     return ok();
 }
 
+int cs_release_cached_memory(void) {
+    cs::dev_release();
+    return ok();
+}
+
 long long cs_lattice_volume(cs_lattice lat) { return lat ? lat->g.V : 0; }
 
 size_t cs_field_bytes(cs_lattice lat, cs_prec prec, int nrhs) {

@@ -166,6 +166,12 @@ void dev_wait(const void* p) {
     }
 }
 
+void dev_release() {
+    Cache& c = cache();
+    std::lock_guard<std::mutex> lk(c.mu);
+    trim(c, -1, 0);
+}
+
 void dev_lattice_created() {
     Cache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);

@@ -19,6 +19,8 @@
 //     then tried again);
 //   * destroying a handle waits for the device (dev_wait), as the hipFree calls
 //     did: what a caller queued with the handle has run when it is gone;
+//   * other allocators of the process cannot reach the kept blocks; a caller
+//     that needs them back uses dev_release (cs_release_cached_memory);
 //   * contents are not cleared, as with hipMalloc.
 // All calls may be made from any thread.
 #pragma once
@@ -35,6 +37,9 @@ void dev_free(void* p);  // p may be null
 // Waits for all work on the device that the block p (handed out, or null)
 // belongs to.
 void dev_wait(const void* p);
+
+// Gives all kept blocks back.
+void dev_release();
 
 // Lattice handles alive (a handle is created / destroyed): blocks are kept
 // only while there is one.

@@ -144,12 +144,23 @@ static int wait() {  // by the probe's free, else by returning kept blocks, else
     dev_wait(nullptr);
     return 0;
 }
+static int release() {
+    void *a, *b;
+    CHECK(dev_alloc(&a, 40) == hipSuccess && dev_alloc(&b, 50) == hipSuccess);
+    dev_free(a);
+    CHECK(used == 90);
+    dev_release();
+    CHECK(used == 50 && !blocks.count(a) && blocks.count(b));
+    dev_release();
+    return 0;
+}
 
 int main(int, char** v) {
     dev_lattice_created();
     struct { const char* name; int (*f)(); } all[] = {
         {"reuse", reuse}, {"bound", bound}, {"retry", retry}, {"last_lattice", last_lattice}, {"failed_wait", failed_wait},
         {"wait", wait},
+        {"release", release},
     };
     for (auto& t : all)
         if (!std::strcmp(t.name, v[1])) return t.f();
@@ -170,7 +181,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["reuse", "bound", "retry", "last_lattice", "failed_wait", "wait"])
+@pytest.mark.parametrize("case", ["reuse", "bound", "retry", "last_lattice", "failed_wait", "wait", "release"])
 def test_pool(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout

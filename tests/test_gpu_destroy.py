@@ -1,4 +1,5 @@
-"""Destroying a handle waits for the work queued with it."""
+"""Destroying a handle waits for the work queued with it, and the device memory
+that destroyed handles leave with the library can be had back."""
 import pytest
 import torch
 
@@ -40,3 +41,21 @@ def test_destroy_waits_for_queued_work(links, handle):
         cs._lib.cs_gauge_destroy(op.gauge.handle)
         op.gauge.handle = None
     assert done.query()
+
+
+def test_kept_memory_can_be_had_back(links):
+    lat = cs.Lattice(DIMS)
+    U, b = links, lat.new_field(cs.F64)
+    cs.Operator(lat, U, 0.13, 1.0).apply_D(lat.new_field(cs.F64), b, cs.F64)
+    torch.cuda.synchronize()
+    cs.release_cached_memory()
+    free = torch.cuda.mem_get_info()[0]
+    op = cs.Operator(lat, U, 0.13, 1.0)
+    held = free - torch.cuda.mem_get_info()[0]
+    assert held > 2000 * lat.volume  # links and clover terms in every precision: 2.5 KB a site
+    del op
+    assert free - torch.cuda.mem_get_info()[0] == held  # kept for the next operator
+    cs.release_cached_memory()
+    assert torch.cuda.mem_get_info()[0] == free
+    op = cs.Operator(lat, U, 0.13, 1.0)
+    del op, lat
