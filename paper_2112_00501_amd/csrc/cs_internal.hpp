@@ -251,25 +251,6 @@ __host__ __device__ __forceinline__ int block_of_item(const Geom& g, int w) {
 #endif
 }
 
-// Internal (blk, l) of the site with global coordinates c (already wrapped).
-__device__ __forceinline__ void site_to_internal(const Geom& g, const int* c, int* blk, int* l) {
-    *blk = (c[0] >> 2) + g.NB[0] * ((c[1] >> 2) + g.NB[1] * ((c[2] >> 2) + g.NB[2] * (c[3] >> 2)));
-    *l = (c[0] & 3) + 4 * ((c[1] & 3) + 4 * ((c[2] & 3) + 4 * (c[3] & 3)));
-}
-
-// Global coordinates of (blk, l).
-__device__ __forceinline__ void internal_coords(const Geom& g, int blk, int l, int* c) {
-    int r = blk;
-    const int bx = r % g.NB[0]; r /= g.NB[0];
-    const int by = r % g.NB[1]; r /= g.NB[1];
-    const int bz = r % g.NB[2];
-    const int bt = r / g.NB[2];
-    c[0] = bx * 4 + (l & 3);
-    c[1] = by * 4 + ((l >> 2) & 3);
-    c[2] = bz * 4 + ((l >> 4) & 3);
-    c[3] = bt * 4 + (l >> 6);
-}
-
 // Canonical site index of (blk, l).
 __device__ __forceinline__ long long canonical_site(const Geom& g, int blk, int l) {
     const BlockPos p = block_pos(g, blk);

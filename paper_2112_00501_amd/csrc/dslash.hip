@@ -439,13 +439,14 @@ hipError_t launch_tiled(const OpData& op, bool dagger, void* out, const void* in
                                dim3(grid), dim3(BLOCK_SITES), 0, s, op.g, lk, cl, op.kappa, out, in, sub, is, os,
                                nrhs, tile, nitems);
         };
-        auto with_dag = [&](auto dag) {
-            if constexpr (PIN == P_F64 && POUT == P_F64) {
-                if (sub) return go(dag, std::true_type{});
+        if constexpr (PIN == P_F64) {
+            if (sub) {  // b - D x only
+                if (dagger) return hipErrorInvalidValue;
+                go(std::false_type{}, std::true_type{});
+                return hipGetLastError();
             }
-            go(dag, std::false_type{});
-        };
-        dagger ? with_dag(std::true_type{}) : with_dag(std::false_type{});
+        }
+        dagger ? go(std::true_type{}, std::false_type{}) : go(std::false_type{}, std::false_type{});
     }
     return hipGetLastError();
 }

@@ -47,43 +47,10 @@ struct GlobalLinks {
     }
 };
 
-// acc += sum over the two hops in direction MU that the spinor policy wants.
-template <int MU, typename R, typename LS, typename LL>
-__device__ __forceinline__ void hop_dir(const Geom& g, const BlockPos& p, int l, const LS& ls,
-                                        const LL& lk, cpx<R>* acc) {
-    int nl;
-    bool in;
-    int nb = neighbour(g, p, l, MU, +1, &nl, &in);
-    if (ls.want(in)) {
-        cpx<R> psi[12], u[9];
-        ls.template load_nb<R>(nb, nl, in, psi);
-        if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, +1, in), &psi[0].re, 24);
-        lk.template load<R>(p.blk, l, MU, true, u);
-        hop_term<MU, -1>(u, psi, acc);
-    }
-    nb = neighbour(g, p, l, MU, -1, &nl, &in);
-    if (ls.want(in)) {
-        cpx<R> psi[12], u[9];
-        ls.template load_nb<R>(nb, nl, in, psi);
-        if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, -1, in), &psi[0].re, 24);
-        lk.template load<R>(nb, nl, MU, in, u);
-        hop_term<MU, +1>(u, psi, acc);
-    }
-}
-
-template <typename R, typename LS, typename LL>
-__device__ __forceinline__ void hopping_sum(const Geom& g, const BlockPos& p, int l, const LS& ls,
-                                            const LL& lk, cpx<R>* acc) {
-    hop_dir<0, R>(g, p, l, ls, lk, acc);
-    hop_dir<1, R>(g, p, l, ls, lk, acc);
-    hop_dir<2, R>(g, p, l, ls, lk, acc);
-    hop_dir<3, R>(g, p, l, ls, lk, acc);
-}
-
-// The same sum as a loop over the eight hops that is not unrolled: each
-// iteration issues one neighbour's loads, so the registers held by loads in
-// flight stay bounded (for kernels whose other state already fills the
-// register file).
+// acc += the sum over the hops that the spinor policy wants, as a loop over the
+// eight of them that is not unrolled: each iteration issues one neighbour's
+// loads, so the registers held by loads in flight stay bounded (for kernels
+// whose other state already fills the register file).
 template <typename R, typename LS, typename LL>
 __device__ __forceinline__ void hopping_sum_rolled(const Geom& g, const BlockPos& p, int l, const LS& ls,
                                                    const LL& lk, cpx<R>* acc) {

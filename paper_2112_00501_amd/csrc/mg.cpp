@@ -74,7 +74,7 @@ void MgData::drop_graphs() const {
 
 void MgData::release() {
     drop_graphs();
-    for (void** q : {&P, &P16, &V, &tmp, (void**)&Dc, &Dc16, (void**)&rc, (void**)&cv.x, (void**)&sc, (void**)&pa.A}) {
+    for (void** q : {&P, &P16, &V, (void**)&Dc, &Dc16, (void**)&rc, (void**)&cv.x, (void**)&sc, (void**)&pa.A}) {
         if (*q) dev_free(*q);
         *q = nullptr;
     }
@@ -93,7 +93,6 @@ hipError_t MgData::alloc(const Geom& g_, const MgParams& p_) {
     MG_CHK(dev_alloc(&P, field_bytes() * p.nv));
     if (p.transfer_half) MG_CHK(dev_alloc(&P16, spinor_bytes_per_site(P_F16) * g.V * p.nv));
     MG_CHK(dev_alloc(&V, field_bytes() * p.nv));
-    MG_CHK(dev_alloc(&tmp, field_bytes()));
     MG_CHK(dev_alloc((void**)&Dc, dc_bytes()));
     if (p.coarse_half) MG_CHK(dev_alloc(&Dc16, dc_bytes() / 2));
     MG_CHK(dev_alloc((void**)&rc, coarse_bytes()));

@@ -46,10 +46,6 @@ __device__ __forceinline__ void block_sum(const float* v, float (*red)[N], float
     __syncthreads();
 }
 
-__device__ __forceinline__ void load_f32(const char* P, size_t fs, int i, int nblk, int blk, int l, cpx<float>* c) {
-    SpinorIO<P_F32>::load(P + (size_t)i * fs, nblk, blk, l, c);
-}
-
 // Block index one step in direction mu (dir = +1 / -1) with periodic wrap.
 __device__ __forceinline__ int block_step(const Geom& g, const BlockPos& p, int mu, int dir) {
     // selected by masks: a select between members of p would be turned into an

@@ -88,7 +88,6 @@ struct MgData {
     void* P = nullptr;
     void* P16 = nullptr;  // FP16 copy (transfer_half)
     void* V = nullptr;
-    void* tmp = nullptr;  // one FP32 field
     float2* Dc = nullptr;
     void* Dc16 = nullptr;  // FP16 copy (coarse_half)
     float2* rc = nullptr;

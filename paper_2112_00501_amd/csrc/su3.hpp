@@ -37,25 +37,13 @@ __device__ __forceinline__ void m3_prod(const cpx<R>* a, const cpx<R>* b, cpx<R>
         }
 }
 
-// c = a b, a b^dag, a^dag b (c may alias a or b)
-template <bool DA, bool DB, typename R>
-__device__ __forceinline__ void m3_prod_alias(const cpx<R>* a, const cpx<R>* b, cpx<R>* c) {
-    cpx<R> t[9];
-    m3_prod<DA, DB, 0>(a, b, t);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) c[i] = t[i];
-}
+// c = a b (c may alias a or b)
 template <typename R>
 __device__ __forceinline__ void m3_mul(const cpx<R>* a, const cpx<R>* b, cpx<R>* c) {
-    m3_prod_alias<false, false>(a, b, c);
-}
-template <typename R>
-__device__ __forceinline__ void m3_mul_nd(const cpx<R>* a, const cpx<R>* b, cpx<R>* c) {
-    m3_prod_alias<false, true>(a, b, c);
-}
-template <typename R>
-__device__ __forceinline__ void m3_mul_dn(const cpx<R>* a, const cpx<R>* b, cpx<R>* c) {
-    m3_prod_alias<true, false>(a, b, c);
+    cpx<R> t[9];
+    m3_prod<false, false, 0>(a, b, t);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) c[i] = t[i];
 }
 
 // c = (or, ACC: +=) h a for a Hermitian h packed as nine reals: the diagonal,
