@@ -153,17 +153,15 @@ __device__ __forceinline__ void hopping_sum_ahead(const Geom& g, const BlockPos&
 // against 33 and 18.4 at 16^3 x 32, 719 against 614 for FP64 at 32^3 x 64.
 // Hops in flight: two in FP64, three below, measured best of 1-3 and 2-5 on
 // lattices of 512 blocks and more (registers: two waves per SIMD in FP32, four
-// in the 16-bit formats).
+// in the 16-bit formats, which are asked for: the BF16 kernel would take one or
+// two registers too many).
 template <int P>
 constexpr int hops_in_flight() { return P == P_F64 ? 2 : 3; }
 
 template <int PIN, int POUT, int PLINK, bool DAG, bool SUB>
-__global__ CS_DSLASH_BOUNDS void k_dslash(Geom g, const void* __restrict__ links,
-                                                        const void* __restrict__ clover, double kappa,
-                                                        void* __restrict__ out,
-                                                        const void* __restrict__ in,
-                                                        const void* __restrict__ sub,
-                                                        size_t in_stride, size_t out_stride) {
+__global__ __launch_bounds__(BLOCK_SITES, PLINK == P_F16 || PLINK == P_BF16 ? 4 : 1) void k_dslash(
+    Geom g, const void* __restrict__ links, const void* __restrict__ clover, double kappa, void* __restrict__ out,
+    const void* __restrict__ in, const void* __restrict__ sub, size_t in_stride, size_t out_stride) {
     using R = typename Arith<PIN>::R;
     const int blk = block_of_item(g, xcd_remap(blockIdx.x, g.nblk)), l = threadIdx.x, r = blockIdx.y;
     const char* src = (const char*)in + r * in_stride;
