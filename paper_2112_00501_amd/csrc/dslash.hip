@@ -146,7 +146,7 @@ __device__ __forceinline__ void hopping_sum_ahead(const Geom& g, const BlockPos&
 
 // One right-hand side per workgroup.  Bound by HBM on large lattices (per
 // site the FP32 operator cannot do without 672 bytes: 32^3 x 64 takes 300 us,
-// 4.7 TB/s of them, with 1.27 times as many crossing the L2) and by the chain
+// 4.7 TB/s of them, with 1.18 times as many crossing the L2) and by the chain
 // of loads on small ones, where a launch is a round or two of workgroups.
 // With the loop over hops not unrolled every hop waited for its own loads:
 // 13.3 us at 8^4 in FP64 and 13.1 in FP32 against 9.9 and 7.8 now, 47 and 21.6
@@ -196,10 +196,11 @@ __global__ __launch_bounds__(BLOCK_SITES, PLINK == P_F16 || PLINK == P_BF16 ? 4 
 }
 
 // Variant for several right-hand sides in FP64, and in FP32 for tiles of three
-// and more: work item = (block, tile of right-hand sides).  The block's links go to LDS once and its clover term to registers
-// once per item; every right-hand side of the tile reuses them.  Backward
-// links of neighbours outside the block come from HBM (cache).  With
-// gridDim.x < nitems the workgroups stride over the items (persistent).
+// and more: work item = (block, tile of right-hand sides).  The block's links go
+// to LDS once and its clover term to registers once per item; every right-hand
+// side of the tile reuses them.  Backward links of neighbours outside the block
+// come from HBM (cache).  With gridDim.x < nitems the workgroups stride over the
+// items (persistent).
 template <typename RS, int PLINK>
 struct MixedLinks {
     const lds_cpx<RS> (*sm)[6][BLOCK_SITES];
@@ -476,11 +477,11 @@ hipError_t launch3(const OpData& op, bool dagger, void* out, const void* in, con
 // a staged tile its links and clover term (head), a unit per right-hand side and
 // what an odd one costs on top; the grouped kernel for two and for three
 // right-hand sides; the untiled kernel.  Fitted at 8^4 to 32^3 x 64 with 2 to 16
-// right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.  In FP64 sharing pays where links, clover term and a field
-// leave the 256 MB cache (24^3 x 48 with 12: 2.41 ms untiled, 2.03 in tiles of
-// six; 16^3 x 32 with 5: 151 us untiled, 157 in one tile).  Two workgroups per
-// compute unit or less have nothing to gain by sharing (8^4 with 12: 9 us
-// untiled, 11 in pairs).
+// right-hand sides; a unit is about 9 us below FP64 and 14 us in FP64.  In FP64
+// sharing pays where links, clover term and a field leave the 256 MB cache
+// (24^3 x 48 with 12: 2.41 ms untiled, 2.03 in tiles of six; 16^3 x 32 with 5:
+// 151 us untiled, 157 in one tile).  Two workgroups per compute unit or less
+// have nothing to gain by sharing (8^4 with 12: 9 us untiled, 11 in pairs).
 struct DslashModel {
     int slots;
     double head, odd;

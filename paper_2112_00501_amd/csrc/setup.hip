@@ -148,9 +148,11 @@ __device__ __forceinline__ C64 herm_entry(const double* h, int a, int b) {
 // of the packed matrix is stored as soon as its planes are done: with the six
 // planes in a loop over tables and the matrix held to the end, 1.5 KB per lane
 // lived in scratch memory, and 32^3 x 64 took 8.7 ms where it now takes 1.3
-// (FP64 issue: 60 products of 108 FMA a site are 0.9 ms at two waves per SIMD;
-// the 72 link reads a site come from cache).  The FP32 copy is left to
-// k_clover_invert, which reads the result anyway.
+// (FP64 issue: 9,000 instructions a wave of 64 sites, 60 products of 108 FMA and
+// the third rows of 72 links, are 0.5 to 0.6 ms at the 4.2 to 5 cycles that one
+// takes; the rest waits for those links, 6.9 KB a site from cache, with two
+// waves per SIMD).  The FP32 copy is left to k_clover_invert, which reads the
+// result anyway.
 __global__ __launch_bounds__(TPB, 2) void k_clover_build(Geom g, const double2* links, double kappa, double csw,
                                                          double2* c64) {
     const int blk = block_of_item(g, xcd_remap(blockIdx.x, g.nblk)), l = threadIdx.x;
