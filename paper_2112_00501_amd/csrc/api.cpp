@@ -456,12 +456,15 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     hipError_t err = cs::blas_fill_pattern(bc, prec, bb, s);
-    // Candidates: tile 1 and the three best by the model among those within
-    // 12 % of the least (the model leaves out caches and clocks), as a grid of
-    // all work items and as a persistent one, and for the smoother one and two
-    // lanes per site while both can be the faster (past 512 visits of a colour
-    // one lane always was).  The model does not fit the FP64 smoother, which
-    // keeps nothing between right-hand sides: a spread of tiles there.
+    // Candidates: tile 1 and the best by the model among those within 12 % of the
+    // least (the model leaves out caches and clocks), as a grid of all work
+    // items and as a persistent one.  The operator takes three of them, the
+    // smoother seven, or three for each of one and two lanes per site while both
+    // can be the faster (past 512 visits of a colour one lane always was): its
+    // best is not always among the first three (24^3 x 48 with 24 right-hand
+    // sides, tiles ranked first, third and fourth: 298, 295 and 294 us each).
+    // The model does not fit the FP64 smoother, which keeps nothing between
+    // right-hand sides: a spread of tiles there.
     struct Cand {
         int kind;  // 0: smoother, 1: operator
         cs::LaunchCfg lc;
@@ -474,6 +477,7 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
                 return kind == 0 ? cs::sap_tile_units(g->g, nrhs, t, lanes) : cs::dslash_tile_units(g->g, prec, nrhs, t);
             };
             const int most = nrhs < 64 ? nrhs : 64;
+            const size_t take = kind == 0 && !both ? 7 : 3;
             std::vector<int> tiles;
             if (kind == 0 && prec == CS_F64) {
                 for (int t : {4, 8, 12})
@@ -483,7 +487,7 @@ static int autotune(cs_gauge g, cs_clover c, int prec, int nrhs, hipStream_t s, 
                 for (int t = 1; t <= most; ++t) ranked.emplace_back(units(t), t);
                 std::sort(ranked.begin(), ranked.end());
                 for (const auto& [u, t] : ranked)
-                    if (t > 1 && u <= 1.12 * ranked[0].first && tiles.size() < 3) tiles.push_back(t);
+                    if (t > 1 && u <= 1.12 * ranked[0].first && tiles.size() < take) tiles.push_back(t);
             }
             tiles.push_back(1);
             for (int t : tiles)

@@ -1,6 +1,7 @@
 """The autotuner times a bounded number of launch shapes, however large the
-batch: four tiles, each as a grid and as a persistent launch, and one lane per
-site where a batch of this size cannot be faster with two."""
+batch: each tile as a grid and as a persistent launch, four tiles for the
+operator and for the FP64 smoother, and below FP64 eight tiles of the smoother
+with one lane per site, where a batch of this size cannot be faster with two."""
 import pytest
 import torch
 
@@ -25,6 +26,6 @@ def test_shapes_timed_are_bounded(prec):
         cs.profile_enable(False)
         cs.profile_reset()
     # a shape is run once and timed three times; a smoother run is four half-sweeps
-    assert 0 < n_sap <= 8 * 4 * 4 and n_sap % 32 == 0
+    assert 0 < n_sap <= (8 if prec == cs.F64 else 16) * 4 * 4 and n_sap % 32 == 0
     assert 0 < n_d <= 8 * 4 and n_d % 8 == 0
     assert 1 <= sap.rhs_tile <= NRHS and 1 <= d.rhs_tile <= NRHS
