@@ -109,7 +109,7 @@ struct RawHop {
             if (MU == 3) time_boundary_phase(g, wraps_time(g, p, MU, DIR, ((l >> 6) & 3) != lc), &c[0].re, 24);
             if (j == 0) {
                 link.get(u);
-                su3_row2(u);
+                su3_row2<std::is_same<R, float>::value>(u);
             }
             hop_term<MU, -DIR>(u, c, acc[j]);
 #pragma unroll
@@ -210,9 +210,9 @@ struct MixedLinks {
         if (inside) {
 #pragma unroll
             for (int k = 0; k < 6; ++k) u[k] = {(R)sm[mu][k][l].re, (R)sm[mu][k][l].im};
-            su3_row2(u);
+            su3_row2<std::is_same<R, float>::value>(u);
         } else {
-            load_link<PLINK, R, false>(base, blk, l, mu, u);
+            load_link<PLINK, R, false, std::is_same<R, float>::value>(base, blk, l, mu, u);
         }
     }
 };

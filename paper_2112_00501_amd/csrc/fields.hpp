@@ -159,21 +159,41 @@ struct SpinorIO<P_BF16> : SpinorIO16<P_BF16> {};
 // ---------------------------------------------------------------------- links
 
 // Row 2 of an SU(3) matrix from rows 0 and 1: conj(row0 x row1).  The
-// roundings are spelled out (each complex product a product and an FMA, then
-// their difference), so that every kernel rebuilds the same bits whatever the
-// compiler contracts around it.
-template <typename R>
+// roundings are spelled out, so that every kernel rebuilds the same bits
+// whatever the compiler contracts around it.  SPLIT: each complex product a
+// product and an FMA, then their difference; else one product and three FMA.
+// The split form rounds a little less (FP32 operator 9.65e-8 from 64 bits, 9.67e-8
+// with the other) and costs two instructions more per entry.  The operator in
+// float arithmetic takes it, where memory hides it, and so does everything with
+// 16-bit links, whose smoother carries a flipped rounding on from colour to
+// colour.  The other smoothers, which rebuild the row in every backward hop, do
+// not (general half-sweep at 32^3 x 64: FP32 298 us, 304 with it, FP64 1197 and
+// 1233), nor do the FP64 kernels.
+template <bool SPLIT, typename R>
 __device__ __forceinline__ cpx<R> conj_minor(cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d) {  // conj(a b - c d)
-    const R pr = fma(a.re, b.re, -(a.im * b.im)), pi = fma(a.im, b.re, a.re * b.im);
-    const R qr = fma(c.re, d.re, -(c.im * d.im)), qi = fma(c.im, d.re, c.re * d.im);
-    return {pr - qr, qi - pi};
+    if constexpr (SPLIT) {
+        const R pr = fma(a.re, b.re, -(a.im * b.im)), pi = fma(a.im, b.re, a.re * b.im);
+        const R qr = fma(c.re, d.re, -(c.im * d.im)), qi = fma(c.im, d.re, c.re * d.im);
+        return {pr - qr, qi - pi};
+    } else {
+        R re = a.re * b.re, im = -(a.re * b.im);
+        re = fma(-a.im, b.im, re);
+        im = fma(-a.im, b.re, im);
+        re = fma(-c.re, d.re, re);
+        im = fma(c.re, d.im, im);
+        re = fma(c.im, d.im, re);
+        im = fma(c.im, d.re, im);
+        return {re, im};
+    }
 }
-template <typename R>
+template <bool SPLIT, typename R>
 __device__ __forceinline__ void su3_row2(cpx<R>* u) {
-    u[6] = conj_minor(u[1], u[5], u[2], u[4]);
-    u[7] = conj_minor(u[2], u[3], u[0], u[5]);
-    u[8] = conj_minor(u[0], u[4], u[1], u[3]);
+    u[6] = conj_minor<SPLIT>(u[1], u[5], u[2], u[4]);
+    u[7] = conj_minor<SPLIT>(u[2], u[3], u[0], u[5]);
+    u[8] = conj_minor<SPLIT>(u[0], u[4], u[1], u[3]);
 }
+template <int P>
+constexpr bool SPLIT_LINKS = P == P_F16 || P == P_BF16;
 
 template <int P>
 struct LinkIO;
@@ -252,14 +272,14 @@ template <>
 struct LinkIO<P_BF16> : LinkIO16<P_BF16> {};
 
 // Full 3x3 link (row 2 rebuilt) in arithmetic type R.
-template <int P, typename R, bool ONCE = true>
+template <int P, typename R, bool ONCE = true, bool SPLIT = SPLIT_LINKS<P>>
 __device__ __forceinline__ void load_link(const void* base, int blk, int l, int mu, cpx<R>* u) {
     using RS = typename LinkIO<P>::R;
     cpx<RS> t[6];
     LinkIO<P>::template load6<ONCE>(base, blk, l, mu, t);
 #pragma unroll
     for (int k = 0; k < 6; ++k) u[k] = {(R)t[k].re, (R)t[k].im};
-    su3_row2(u);
+    su3_row2<SPLIT>(u);
 }
 
 // --------------------------------------------------------------------- clover

@@ -92,7 +92,7 @@ __device__ __forceinline__ void block_hop_fetch(int l, const LdsSpinor<float>& l
 // computed: with a wave or two per SIMD nothing else hides that latency.  Four
 // MR steps of a block take 36.5 thousand cycles with two workgroups per CU and
 // 32.5 alone; fetching each hop when it was due, 39 and 36.6.
-template <int H = 0>
+template <bool SPLIT, int H = 0>
 __device__ __forceinline__ void block_hops_from(int l, const LdsSpinor<float>& ls, const LinkSmem<true>& sm,
                                                 const OwnRow2& own, const BlockHop& cur, cpx<float>* acc) {
     constexpr int MU = H / 2;
@@ -106,20 +106,20 @@ __device__ __forceinline__ void block_hops_from(int l, const LdsSpinor<float>& l
         for (int k = 0; k < 3; ++k) u[6 + k] = own.r[MU][k];
         hop_term<MU, -1>(u, cur.psi, acc);
     } else {
-        su3_row2(u);
+        su3_row2<SPLIT>(u);
         hop_term<MU, +1>(u, cur.psi, acc);
     }
     if constexpr (H < 7) {
         __builtin_amdgcn_sched_barrier(0);
-        block_hops_from<H + 1>(l, ls, sm, own, next, acc);
+        block_hops_from<SPLIT, H + 1>(l, ls, sm, own, next, acc);
     }
 }
-template <typename R>
+template <bool SPLIT, typename R>
 __device__ __forceinline__ void block_hops(int l, const LdsSpinor<R>& ls, const LinkSmem<true>& sm,
                                            const OwnRow2& own, cpx<R>* acc) {
     BlockHop first;
     block_hop_fetch<0>(l, ls, sm, first);
-    block_hops_from<0>(l, ls, sm, own, first, acc);
+    block_hops_from<SPLIT, 0>(l, ls, sm, own, first, acc);
 }
 
 // x is zero on the blocks of the current colour: only hops that leave the
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256, P != P_F64 && BS != BLOCK_EO ? 2 : 1) void k_s
                     uf[k] = {(float)u[k].re, (float)u[k].im};
                     s_lk.u[mu][k][l].set(uf[k]);
                 }
-                su3_row2(uf);
+                su3_row2<SPLIT_LINKS<PLINK>>(uf);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) own.r[mu][k] = uf[6 + k];
             }
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(256, P != P_F64 && BS != BLOCK_EO ? 2 : 1) void k_s
 #pragma unroll
                     for (int k = 0; k < 12; ++k) s_rho[k][l] = {(R)t[k].re, (R)t[k].im};
                     __syncthreads();
-                    block_hops<R>(l, ls, s_lk, own, acc);
+                    block_hops<SPLIT_LINKS<PLINK>, R>(l, ls, s_lk, own, acc);
                 }
                 int lf = l;
                 hold(acc, lf);
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(256, P != P_F64 && BS != BLOCK_EO ? 2 : 1) void k_s
 #pragma unroll
                     for (int k = 0; k < 12; ++k) acc[k] = {(R)0, (R)0};
                     if constexpr (F32PATH) {
-                        block_hops<R>(l, ls, s_lk, own, acc);
+                        block_hops<SPLIT_LINKS<PLINK>, R>(l, ls, s_lk, own, acc);
                         clover_apply(cl, acc, delta);
                     } else {
                         GlobalLinks<PLINK, false> lk{links};
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(256, P != P_F64 && BS != BLOCK_EO ? 2 : 1) void k_s
 #pragma unroll
                     for (int k = 0; k < 12; ++k) acc[k] = {(R)0, (R)0};
                     if constexpr (F32PATH) {
-                        block_hops<R>(l, ls, s_lk, own, acc);
+                        block_hops<SPLIT_LINKS<PLINK>, R>(l, ls, s_lk, own, acc);
                     } else {
                         GlobalLinks<PLINK, false> lk{links};
                         hopping_sum_rolled<R>(g, p, l, ls, lk, acc);
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(256, P != P_F64 && BS != BLOCK_EO ? 2 : 1) void k_s
 #pragma unroll
                     for (int k = 0; k < 12; ++k) acc[k] = {(R)0, (R)0};
                     if constexpr (F32PATH) {
-                        block_hops<R>(l, ls, s_lk, own, acc);
+                        block_hops<SPLIT_LINKS<PLINK>, R>(l, ls, s_lk, own, acc);
                     } else {
                         GlobalLinks<PLINK, false> lk{links};
                         hopping_sum_rolled<R>(g, p, l, ls, lk, acc);

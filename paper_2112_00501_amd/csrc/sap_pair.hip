@@ -356,7 +356,7 @@ __global__ __launch_bounds__(PAIR_TPB) void k_sap_pair(Geom g, const void* __res
             cpx<float> u[9];
 #pragma unroll
             for (int k = 0; k < 6; ++k) u[k] = {(float)lw[j][k].re, (float)lw[j][k].im};
-            su3_row2(u);
+            su3_row2<SPLIT_LINKS<PLINK>>(u);
 #pragma unroll
             for (int k = 0; k < 9; ++k) sm.u[2 * q.h + j][k][q.l].set(u[k]);
         }

@@ -60,7 +60,7 @@ __device__ __forceinline__ void link_at(const double2* p, int d, C64* u) {
         const double2 v = p[(d * 6 + k) * BLOCK_SITES];
         u[k] = {v.x, v.y};
     }
-    su3_row2(u);
+    su3_row2<false>(u);
 }
 
 // A = Q - Q^dag of the plane (MU, NU) with Q_{mu nu}(x) the four
