@@ -405,7 +405,7 @@ struct LaunchCfg {
 // once for its tile), and the launch as many rounds as the slots need for all
 // workgroups, so a tile that leaves a round nearly empty loses to one that
 // fills it (FP32 smoother, 12 right-hand sides of 256 blocks a colour in 512
-// slots: tiles of 4 and 8 take 735 and 852 us, 3 and 6 take 679 and 671).
+// slots: tiles of 4 and 8 take 730 and 836 us, 3 and 6 take 665 and 647).
 inline int tile_for(long long blocks, int nrhs, int slots, double head) {
     int best = 1;
     double least = 0;

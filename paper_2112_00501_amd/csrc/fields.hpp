@@ -166,9 +166,9 @@ struct SpinorIO<P_BF16> : SpinorIO16<P_BF16> {};
 // with the other) and costs two instructions more per entry.  The operator in
 // float arithmetic takes it, where memory hides it, and so does everything with
 // 16-bit links, whose smoother carries a flipped rounding on from colour to
-// colour.  The other smoothers, which rebuild the row in every backward hop, do
-// not (general half-sweep at 32^3 x 64: FP32 298 us, 304 with it, FP64 1197 and
-// 1233), nor do the FP64 kernels.
+// colour (general half-sweep at 32^3 x 64: BF16 269 us, 265 with the other).  The
+// other smoothers, which rebuild the row in every backward hop too, do not (FP32
+// 298 us, 304 with it, FP64 1197 and 1233), nor do the FP64 kernels.
 template <bool SPLIT, typename R>
 __device__ __forceinline__ cpx<R> conj_minor(cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d) {  // conj(a b - c d)
     if constexpr (SPLIT) {

@@ -809,8 +809,8 @@ hipError_t launch_p(const OpData& op, int colour, int n_mr, int mode, void* x, c
 // MI355X): measured 7-8% faster at 128 and 256 blocks per colour, 16% slower
 // at 648 and 45% at 1296 and 4096.  The line is drawn by the lattice alone,
 // although a batch past 256 visits of a colour is faster with one lane
-// (16^3 x 32, two cycles in their best tiles: two right-hand sides 173 us and
-// 158, twelve 866 and 671): the kernels sum in different orders, and a
+// (16^3 x 32, two cycles in their best tiles: two right-hand sides 172 us and
+// 155, twelve 861 and 647): the kernels sum in different orders, and a
 // right-hand side keeps the result of its own call whatever it is batched with.
 int sap_default_lanes(const Geom& g, int prec, int block_solver) {
     if (prec == P_F64 || block_solver == BLOCK_EO) return 1;  // have the one-lane form only

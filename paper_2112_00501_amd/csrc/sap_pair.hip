@@ -43,7 +43,7 @@ __device__ __forceinline__ PairLane pair_lane() {
 // lies outside the block reads a zero instead of branching: the one in the bank
 // of the site it would wrap to, which no other lane then reads (one zero for
 // all lanes met other lanes' banks: 79.6 us a cycle pair at 8^4 in FP32 against
-// 77.1 now, 106.0 against 103.8 at 16^3 x 32).  The links are kept whole (all
+// 76.8 now, 106.0 against 103.2 at 16^3 x 32).  The links are kept whole (all
 // three rows), rebuilt once when staged.
 constexpr int RHO_STRIDE = BLOCK_SITES + 64;
 constexpr int ZERO_SITE = BLOCK_SITES;
