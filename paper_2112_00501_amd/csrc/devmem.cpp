@@ -44,6 +44,17 @@ struct OnDevice {
     }
 };
 
+// Calls that are not capturable are allowed in this thread for the lifetime of
+// the object, without ending a stream capture that is open in it.
+struct BesideCapture {
+    hipStreamCaptureMode was = hipStreamCaptureModeRelaxed;
+    bool set;
+    BesideCapture() : set(hipThreadExchangeStreamCaptureMode(&was) == hipSuccess) {}
+    ~BesideCapture() {
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&was);
+    }
+};
+
 void free_block(const Block& b) {
     OnDevice on(b.dev);
     (void)hipFree(b.p);
@@ -156,6 +167,7 @@ void dev_wait(const void* p) {
     auto it = c.live.find(const_cast<void*>(p));
     if (it == c.live.end()) return;
     const int dev = it->second.dev;
+    BesideCapture beside;  // a handle may go while its thread captures
     if (wait_for_device(c, dev) == hipSuccess) return;
     // no memory left for the wait: returning kept blocks waits too
     if (c.kept_bytes[dev] > 0) {
@@ -169,6 +181,7 @@ void dev_wait(const void* p) {
 void dev_release() {
     Cache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
+    BesideCapture beside;
     trim(c, -1, 0);
 }
 

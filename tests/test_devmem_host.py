@@ -13,6 +13,8 @@ STUB = r"""
 #pragma once
 #include <cstddef>
 enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2 };
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m);
 hipError_t hipMalloc(void** p, size_t n);
 hipError_t hipFree(void* p);
 hipError_t hipGetDevice(int* d);
@@ -55,6 +57,13 @@ hipError_t hipFree(void* p) {
     blocks.erase(p);
     pending = false;  // waits for the device
     ++waits;
+    return hipSuccess;
+}
+static hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+    const hipStreamCaptureMode was = mode;
+    mode = *m;
+    *m = was;
     return hipSuccess;
 }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -138,7 +147,7 @@ static int wait() {  // by the probe's free, else by returning kept blocks, else
         if (k == 1) dev_free(b);
         pending = true;
         dev_wait(a);
-        CHECK(!pending && hipGetLastError() == hipSuccess);
+        CHECK(!pending && hipGetLastError() == hipSuccess && mode == hipStreamCaptureModeGlobal);
     }
     CHECK(used == 40);
     dev_wait(nullptr);

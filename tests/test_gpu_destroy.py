@@ -59,3 +59,22 @@ def test_kept_memory_can_be_had_back(links):
     assert torch.cuda.mem_get_info()[0] == free
     op = cs.Operator(lat, U, 0.13, 1.0)
     del op, lat
+
+
+def test_destroy_leaves_an_open_capture_valid(links):
+    lat = cs.Lattice(DIMS)
+    op, other = cs.Operator(lat, links, 0.13, 1.0), cs.Operator(lat, links, 0.12, 1.0)
+    b = lat.new_field(cs.F32)
+    b.view(torch.float32).normal_()
+    ref = op.apply_D(lat.new_field(cs.F32), b, cs.F32)
+    out = lat.new_field(cs.F32).zero_()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        op.apply_D(out, b, cs.F32)
+        del other
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
